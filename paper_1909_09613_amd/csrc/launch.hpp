@@ -36,9 +36,17 @@ struct SortArgs {
 };
 
 // Block size and LDS bytes of the per-segment arrange pass of the sort.
+// Segments of up to kArrangeCap particles (kArrangeItems per thread) are
+// ordered by place within their cells (those of up to kArrangeOrderCount
+// particles), in tiles of up to kArrangeOrderCells cells (the tables of larger
+// ones leave no room for the keys in 64 KB).
 constexpr int kArrangeBlock = 512;
+constexpr int kArrangeItems = 16;
+constexpr int kArrangeCap = kArrangeItems * kArrangeBlock;
+constexpr int kArrangeOrderCells = 2048, kArrangeOrderCount = 64;
 inline size_t arrange_lds(int tc, int kcap) {
-  return (size_t)4 * (2 * tc + kcap + 2) + (size_t)2 * kcap * tc + 16;
+  const size_t keys = tc <= kArrangeOrderCells ? (size_t)2 * (tc + kArrangeCap) : 0;
+  return (size_t)4 * (2 * tc + kcap + 2) + (size_t)2 * kcap * tc + keys + 16;
 }
 // Levels the arrange pass orders one by one for a tile of tc cells.
 inline int arrange_kcap(int tc) {

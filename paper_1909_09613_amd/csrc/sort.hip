@@ -10,7 +10,7 @@
 // arrange  one block per segment: order the segment back into the current
 //          store by (rank within its cell, cell): first every cell's first
 //          particle, cells in tile order, then every cell's second particle,
-//          and so on.  The lanes of a wave then hold particles of 64
+//          and so on, ranked by their place in the cell.  The lanes of a wave then hold particles of 64
 //          nearby cells, one each, so that the gather reads and the current
 //          atomics of a wave touch distinct, nearly consecutive LDS
 //          addresses.  Ranks beyond `kcap` (dense cells) follow in cell order.
@@ -194,14 +194,7 @@ __global__ void sort_scatter(SortArgs<typename P::Real> A) {
 // precision 32x16 and 64x8 1-6% faster without it, 16x16 and 16x32 8-10%
 // faster with it; 3D mixed precision 3% faster without it.
 template <class P, int DIM>
-__device__ __forceinline__ int cell_in_tile(const PBuf<typename P::Real>& S, long long q, const int org[3],
-                                            const int tile[3]) {
-  int c[3] = {0, 0, 0};
-  if (P::kAbs) {
-    for (int d = 0; d < DIM; ++d) c[d] = (int)floor(S.pos[d][q]);
-  } else {
-    unpack_cell<DIM>(S.cell[q], c[0], c[1], c[2]);
-  }
+__device__ __forceinline__ int cell_index(const int c[3], const int org[3], const int tile[3]) {
   int m[3] = {0, 0, 0};
   for (int d = 0; d < DIM; ++d) m[d] = min(max(c[d] - org[d], 0), tile[d] - 1);
   if ((P::kAbs || (DIM == 2 && tile[0] < 32)) && (tile[0] & 1) == 0) {
@@ -219,6 +212,39 @@ __device__ __forceinline__ int cell_in_tile(const PBuf<typename P::Real>& S, lon
 }
 
 template <class P, int DIM>
+__device__ __forceinline__ int cell_in_tile(const PBuf<typename P::Real>& S, long long q, const int org[3],
+                                            const int tile[3]) {
+  int c[3] = {0, 0, 0};
+  if (P::kAbs) {
+    for (int d = 0; d < DIM; ++d) c[d] = (int)floor(S.pos[d][q]);
+  } else {
+    unpack_cell<DIM>(S.cell[q], c[0], c[1], c[2]);
+  }
+  return cell_index<P, DIM>(c, org, tile);
+}
+
+// Order of a particle among those of its cell, as a 16-bit key: its offset
+// along x1, and in 3D first the half of the cell along x2 that it lies in.
+// The lanes of a wave hold one particle each of consecutive cells along x1,
+// all of the same rank, so with ranks in the order of the offset they lie at
+// about the same place in their cells.  Their stencils then mostly start at
+// the same node of their cell, and the lanes' LDS addresses stay distinct and
+// consecutive; where some lanes start one node further than others, the reads
+// conflict and the atomics of neighbouring cells meet at one address (LDS
+// cycles per 64-lane access at rows of 32 cells, with every lane's start
+// random: reads 3.4 against 2.7, 32-bit adds 6.5 against 4.5, FP64 adds 20.8
+// against 8.6).  A drift moves all particles of the wave alike and keeps the
+// order.  Particle kernel, against ranks in arrival order: 2D cubic 1024x512
+// mixed precision 347 -> 326 us, 777x389 FP64 334 -> 310 us; 3D quadratic
+// 128x128x64 mixed precision 779 -> 711 us (752 by the offset alone),
+// 96x64x64 FP64 716 -> 682 us.
+template <class Real, int DIM>
+__device__ __forceinline__ unsigned order_key(Real fx, Real fy) {
+  if (DIM == 2) return (unsigned)((float)fx * 65535.0f);
+  return (fy >= Real(0.5) ? 32768u : 0u) + (unsigned)((float)fx * 32767.0f);
+}
+
+template <class P, int DIM>
 __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
   if (!A.st->sort_request) return;
@@ -229,8 +255,11 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
   int* xpre = cnt + TC;                                         // TC + 1: prefix of ranks >= KC
   int* base = xpre + TC + 1;                                    // KC + 1: slots below level k
   unsigned short* pre = reinterpret_cast<unsigned short*>(base + KC + 1);  // KC x TC
+  unsigned short* first = pre + KC * TC;                        // TC: first key of a cell in keys
+  unsigned short* keys = first + TC;                            // kArrangeCap: keys by cell
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int nwave = kArrangeBlock / 64;
+  constexpr int U = kArrangeItems, V = 4;
   const int par = A.st->parity;
   const PBuf<Real> S = A.buf[par ^ 1];
   const PBuf<Real> D = A.buf[par];
@@ -248,13 +277,55 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
     org[0] = (lt % R.ntile[0]) * A.tile[0];
     org[1] = ((lt / R.ntile[0]) % R.ntile[1]) * A.tile[1];
     org[2] = (DIM == 3) ? (lt / (R.ntile[0] * R.ntile[1])) * A.tile[2] : 0;
+    // a segment of up to kArrangeCap particles keeps each particle's cell and
+    // rank in registers and orders the cells; a larger one (dense cells, or
+    // more particles per cell than any workload here has) takes the arrival
+    // order, its ranks through global memory
+    const bool ordered = TC <= kArrangeOrderCells && n <= kArrangeCap;
     for (int i = tid; i < TC; i += kArrangeBlock) cnt[i] = 0;
     if (tid == 0) cmax_s = 0;
     __syncthreads();
-    // rank of each particle within its cell
-    for (int i = tid; i < n; i += kArrangeBlock) {
-      const long long q = s0 + (long long)i;
-      A.keys[q] = atomicAdd(&cnt[cell_in_tile<P, DIM>(S, q, org, A.tile)], 1);
+    // rank of each particle within its cell, in arrival order
+    int cell_of[U], rank_of[U];
+    if (ordered) {
+#pragma unroll
+      for (int u0 = 0; u0 < U; u0 += V) {
+        if (u0 * kArrangeBlock >= n) break;
+        Real x[V][3];
+        int pc[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const int q = s0 + min(tid + (u0 + v) * kArrangeBlock, n - 1);
+          pc[v] = P::kAbs ? 0 : S.cell[q];
+#pragma unroll
+          for (int d = 0; d < DIM; ++d)
+            if (P::kAbs || d < 2) x[v][d] = S.pos[d][q];
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          int c[3] = {0, 0, 0};
+          if (P::kAbs) {
+#pragma unroll
+            for (int d = 0; d < DIM; ++d) {
+              const Real fl = floor(x[v][d]);
+              c[d] = (int)fl;
+              x[v][d] -= fl;
+            }
+          } else {
+            unpack_cell<DIM>(pc[v], c[0], c[1], c[2]);
+          }
+          const int cl = cell_index<P, DIM>(c, org, A.tile);
+          const unsigned k = order_key<Real, DIM>(x[v][0], x[v][1]);
+          rank_of[u0 + v] = 0;
+          if (tid + (u0 + v) * kArrangeBlock < n) rank_of[u0 + v] = atomicAdd(&cnt[cl], 1);
+          cell_of[u0 + v] = cl | (int)(k << 16);
+        }
+      }
+    } else {
+      for (int i = tid; i < n; i += kArrangeBlock) {
+        const int q = s0 + i;
+        A.keys[q] = atomicAdd(&cnt[cell_in_tile<P, DIM>(S, q, org, A.tile)], 1);
+      }
     }
     __syncthreads();
     // level k < KC: cells holding more than k particles, numbered in cell order
@@ -269,50 +340,108 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
       }
       if (lane == 0) base[k + 1] = run;
     }
-    // ranks >= KC: exclusive prefix over cells of max(0, count - KC)
-    if (wave == 0) {
+    // exclusive prefixes over cells: of max(0, count - KC) for the ranks
+    // beyond the levels, and of the counts for the keys by cell
+    if (wave == 0 || (wave == 1 && ordered)) {
       int run = 0;
       for (int c0 = 0; c0 < TC; c0 += 64) {
         const int c = c0 + lane;
-        const int v = c < TC ? max(0, cnt[c] - KC) : 0;
+        const int v = c < TC ? (wave == 0 ? max(0, cnt[c] - KC) : cnt[c]) : 0;
         int incl = v;
         for (int off = 1; off < 64; off <<= 1) {
           const int t = __shfl_up(incl, off);
           if (lane >= off) incl += t;
         }
-        if (c < TC) xpre[c] = run + incl - v;
+        if (c < TC) {
+          if (wave == 0) xpre[c] = run + incl - v;
+          else first[c] = (unsigned short)(run + incl - v);
+        }
         run += __shfl(incl, 63);
       }
-      if (lane == 0) xpre[TC] = run;
+      if (wave == 0 && lane == 0) xpre[TC] = run;
     }
     __syncthreads();
     if (tid == 0) {
       base[0] = 0;
       for (int k = 0; k < KC; ++k) base[k + 1] += base[k];
     }
+    if (ordered) {
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (tid + u * kArrangeBlock < n)
+          keys[first[cell_of[u] & 0xffff] + rank_of[u]] = (unsigned short)((unsigned)cell_of[u] >> 16);
+    }
     __syncthreads();
     float mb[3] = {0.0f, 0.0f, 0.0f};
-    for (int i = tid; i < n; i += kArrangeBlock) {
-      const long long q = s0 + (long long)i;
-      const int cl = cell_in_tile<P, DIM>(S, q, org, A.tile);
-      if (!P::kAbs) {
-        // bounds of the next step's current contributions (see gpd.hip):
-        // |step| per axis, and |v3| for the out-of-plane current in 2D
-        const float u0 = (float)S.u[0][q], u1 = (float)S.u[1][q], u2 = (float)S.u[2][q];
-        const float ig = 1.0f / sqrtf(1.0f + u0 * u0 + u1 * u1 + u2 * u2);
-        mb[0] = fmaxf(mb[0], (float)R.a[0] * fabsf(u0) * ig);
-        mb[1] = fmaxf(mb[1], (float)R.a[1] * fabsf(u1) * ig);
-        mb[2] = fmaxf(mb[2], (DIM == 2 ? 1.0f : (float)R.a[2]) * fabsf(u2) * ig);
+    // slot of a particle of cell cl at rank k
+    auto slot_of = [&](int cl, int k) { return (k < KC) ? base[k] + (int)pre[k * TC + cl] : base[KC] + xpre[cl] + (k - KC); };
+    // bounds of the next step's current contributions (see gpd.hip): |step|
+    // per axis, and |v3| for the out-of-plane current in 2D
+    auto bound = [&](float u0, float u1, float u2) {
+      const float ig = 1.0f / sqrtf(1.0f + u0 * u0 + u1 * u1 + u2 * u2);
+      mb[0] = fmaxf(mb[0], (float)R.a[0] * fabsf(u0) * ig);
+      mb[1] = fmaxf(mb[1], (float)R.a[1] * fabsf(u1) * ig);
+      mb[2] = fmaxf(mb[2], (DIM == 2 ? 1.0f : (float)R.a[2]) * fabsf(u2) * ig);
+    };
+    if (ordered) {
+#pragma unroll
+      for (int u0 = 0; u0 < U; u0 += V) {
+        if (u0 * kArrangeBlock >= n) break;
+        int pc[V], tag[V], slot[V];
+        Real x[V][3], uu[V][3];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const int q = s0 + min(tid + (u0 + v) * kArrangeBlock, n - 1);
+          pc[v] = P::kAbs ? 0 : S.cell[q];
+#pragma unroll
+          for (int d = 0; d < DIM; ++d) x[v][d] = S.pos[d][q];
+#pragma unroll
+          for (int d = 0; d < 3; ++d) uu[v][d] = S.u[d][q];
+          tag[v] = S.tag[q];
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          // the rank in the order of the keys (equal keys in arrival order);
+          // a cell too dense for a look at all its keys keeps the arrival order
+          const int cl = cell_of[u0 + v] & 0xffff, m = cnt[cl], f0 = first[cl];
+          const int kv = (int)((unsigned)cell_of[u0 + v] >> 16);
+          int k = rank_of[u0 + v];
+          if (m <= kArrangeOrderCount) {
+            const int r = k;
+            k = 0;
+            for (int j = 0; j < m; ++j) {
+              const int o = keys[f0 + j];
+              k += (o < kv || (o == kv && j < r)) ? 1 : 0;
+            }
+          }
+          slot[v] = slot_of(cl, k);
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          if (tid + (u0 + v) * kArrangeBlock >= n) continue;
+          if (!P::kAbs) bound((float)uu[v][0], (float)uu[v][1], (float)uu[v][2]);
+          const int o = s0 + slot[v];
+          if (!P::kAbs) D.cell[o] = pc[v];
+#pragma unroll
+          for (int d = 0; d < DIM; ++d) D.pos[d][o] = x[v][d];
+#pragma unroll
+          for (int d = 0; d < 3; ++d) D.u[d][o] = uu[v][d];
+          D.tag[o] = tag[v];
+        }
       }
-      const int k = A.keys[q];
-      const int slot = (k < KC) ? base[k] + (int)pre[k * TC + cl] : base[KC] + xpre[cl] + (k - KC);
-      const long long o = s0 + (long long)slot;
-      if (!P::kAbs) D.cell[o] = S.cell[q];
-      for (int d = 0; d < DIM; ++d) D.pos[d][o] = S.pos[d][q];
-      D.u[0][o] = S.u[0][q];
-      D.u[1][o] = S.u[1][q];
-      D.u[2][o] = S.u[2][q];
-      D.tag[o] = S.tag[q];
+    } else {
+      for (int i = tid; i < n; i += kArrangeBlock) {
+        const int q = s0 + i;
+        const int cl = cell_in_tile<P, DIM>(S, q, org, A.tile);
+        if (!P::kAbs) bound((float)S.u[0][q], (float)S.u[1][q], (float)S.u[2][q]);
+        const int o = s0 + slot_of(cl, A.keys[q]);
+        if (!P::kAbs) D.cell[o] = S.cell[q];
+        for (int d = 0; d < DIM; ++d) D.pos[d][o] = S.pos[d][q];
+        D.u[0][o] = S.u[0][q];
+        D.u[1][o] = S.u[1][q];
+        D.u[2][o] = S.u[2][q];
+        D.tag[o] = S.tag[q];
+      }
     }
     if (!P::kAbs) {
       for (int c = 0; c < 3; ++c) {
