@@ -105,6 +105,7 @@ struct RunDev {
   double skip_t0, cd, dtd;
   long long skip_l0;
   int skip_on;
+  TFac<Real> tf[3];   // T_l (WT) or W_l (MC) on the integer lattice, where KT == l + 1
   Tab<Real> Wh[3];    // W_l on the half-integer lattice
   Tab<Real> Wi[3];    // W_l on the integer lattice (charge form factor)
   Tab<Real> T[3];     // T_l (WT) or W_l (MC) on the integer lattice

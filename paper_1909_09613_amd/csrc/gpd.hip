@@ -98,34 +98,44 @@ __device__ __forceinline__ Real gather3(const Real* Fc, int px, int pz, const Re
   return s;
 }
 
-// Weights of a B-spline table's NW nodes at g.  The cubic B-spline of the
-// compile-time tables in its symmetric closed form, 11 instructions against
-// 12 for the four Horner polynomials: with t = 1 - g, w0 = t^3/6,
-// w1 = 2/3 - g^2 + g^3/2, w2 the same at t, w3 = g^3/6 (the coefficients of
-// those tables, checked where they are built).
-template <int L, int NW, bool CONSTTAB, class Real>
+// Weights of a B-spline table's NW nodes at g, up to the cubic one in the
+// closed form of its polynomials (checked where the tables are built).  The
+// cubic in its symmetric form, 11 instructions against 12 for the four Horner
+// polynomials: with t = 1 - g, w0 = t^3/6, w1 = 2/3 - g^2 + g^3/2, w2 the same
+// at t, w3 = g^3/6.  The closed forms need at most two constants that are no
+// immediate operands, where FP64 read both tables from scalar memory for
+// every particle.
+template <int L, int NW, class Real>
 __device__ __forceinline__ void wtab_eval(const Tab<Real>& T, Real g, Real* w) {
-  if constexpr (CONSTTAB && L == 3 && NW == 4) {
+  if constexpr (L == 3 && NW == 4) {
     const Real t = Real(1) - g;
     const Real g2 = g * g, t2 = t * t;
     w[0] = t2 * (t * Real(1.0 / 6.0));
     w[1] = fma(g2, fma(g, Real(0.5), Real(-1)), Real(2.0 / 3.0));
     w[2] = fma(t2, fma(t, Real(0.5), Real(-1)), Real(2.0 / 3.0));
     w[3] = g2 * (g * Real(1.0 / 6.0));
+  } else if constexpr (L == 2 && NW == 3) {
+    const Real t = Real(1) - g;
+    w[0] = t * (t * Real(0.5));
+    w[1] = fma(g, t, Real(0.5));
+    w[2] = g * (g * Real(0.5));
+  } else if constexpr (L == 1 && NW == 2) {
+    w[0] = Real(1) - g;
+    w[1] = g;
   } else {
     tab_eval<L, NW, false>(T, g, w);
   }
 }
 
 // Weight differences w_k(e) - w_k(g) = d * (divided difference), d = e - g,
-// for a table's L + 1 nodes.  For the cubic B-spline of the compile-time
-// tables with h2 = g + e and h3 = g^2 + g e + e^2: the differences of the
-// four closed forms above are d (h3/6), d ((h2 - 1)/2 - h3/6) and
-// d (h3/2 - h2) for nodes 3, 0 and 1, and node 2 takes minus their sum (the
-// weights sum to one), 12 instructions against 16.
+// for a table's L + 1 nodes.  For the cubic B-spline with h2 = g + e and
+// h3 = g^2 + g e + e^2: the differences of the four closed forms above are
+// d (h3/6), d ((h2 - 1)/2 - h3/6) and d (h3/2 - h2) for nodes 3, 0 and 1, and
+// node 2 takes minus their sum (the weights sum to one), 12 instructions
+// against 16; the quadratic one's d h2/2, d (h2/2 - 1) and minus their sum.
 template <int L, bool CONSTTAB, class Real>
 __device__ __forceinline__ void wtab_diff(const Tab<Real>& T, Real g, Real e, Real d, Real* dw) {
-  if constexpr (CONSTTAB && L == 3) {
+  if constexpr (L == 3) {
     const Real h2 = g + e;
     const Real h3 = fma(h2, e, g * g);
     const Real q = h3 * (d * Real(1.0 / 6.0));
@@ -133,20 +143,30 @@ __device__ __forceinline__ void wtab_diff(const Tab<Real>& T, Real g, Real e, Re
     dw[0] = fma(h2 - Real(1), d * Real(0.5), -q);
     dw[1] = fma(Real(3), q, -(d * h2));
     dw[2] = -(dw[0] + dw[1]) - q;
+  } else if constexpr (L == 2) {
+    const Real q = (g + e) * (d * Real(0.5));
+    dw[0] = q - d;
+    dw[1] = fma(Real(-2), q, d);
+    dw[2] = q;
+  } else if constexpr (L == 1) {
+    dw[0] = -d;
+    dw[1] = d;
   } else {
     tab_diff<L, CONSTTAB>(T, g, e, d, dw);
   }
 }
 
-// Whether a table holds the cubic B-spline polynomials in the node order of
-// wtab_eval's closed form.
+// Whether a table of order l <= 3 holds the B-spline polynomials in the node
+// order of wtab_eval's closed forms.
 template <class Real>
-constexpr bool is_cubic_bspline(const Tab<Real>& t) {
-  constexpr double ref[4][4] = {{1.0 / 6, -0.5, 0.5, -1.0 / 6}, {2.0 / 3, 0.0, -1.0, 0.5},
-                                {1.0 / 6, 0.5, 0.5, -0.5}, {0.0, 0.0, 0.0, 1.0 / 6}};
-  for (int k = 0; k < 4; ++k)
-    for (int r = 0; r < 4; ++r) {
-      const double d = (double)t.c[k][r] - ref[k][r];
+constexpr bool is_bspline(const Tab<Real>& t, int l) {
+  constexpr double ref[3][4][4] = {
+      {{1.0, -1.0}, {0.0, 1.0}},
+      {{0.5, -1.0, 0.5}, {0.5, 1.0, -1.0}, {0.0, 0.0, 0.5}},
+      {{1.0 / 6, -0.5, 0.5, -1.0 / 6}, {2.0 / 3, 0.0, -1.0, 0.5}, {1.0 / 6, 0.5, 0.5, -0.5}, {0.0, 0.0, 0.0, 1.0 / 6}}};
+  for (int k = 0; k <= l; ++k)
+    for (int r = 0; r <= l; ++r) {
+      const double d = (double)t.c[k][r] - ref[l - 1][k][r];
       if (d > 1e-6 || d < -1e-6) return false;
     }
   return true;
@@ -194,8 +214,8 @@ __device__ __forceinline__ float in_vgpr(float x) {
 __device__ __forceinline__ float fract_(float x) { return __builtin_amdgcn_fractf(x); }
 __device__ __forceinline__ double fract_(double x) { return __builtin_amdgcn_fract(x); }
 template <class Real>
-__device__ __forceinline__ void split_rt(const Tab<Real>& t, int cell, Real f, int& base, Real& g) {
-  const Real d = f - t.sigma;
+__device__ __forceinline__ void split_rt(Real sigma, int cell, Real f, int& base, Real& g) {
+  const Real d = f - sigma;
   base = cell - (d < Real(0) ? 1 : 0);
   g = fract_(d);
 }
@@ -344,7 +364,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   // B-spline tables on the half-integer and the integer lattice: constants
   constexpr Tab<Real> kWh = make_wtab<Real>(L, 0);
   constexpr Tab<Real> kWi = make_wtab<Real>(L, 1);
-  static_assert(L != 3 || (is_cubic_bspline(kWh) && is_cubic_bspline(kWi)), "cubic tables");
+  static_assert(L > 3 || (is_bspline(kWh, L) && is_bspline(kWi, L)), "B-spline tables");
   const int tid = threadIdx.x;
   const int nth = GpdShape<L, DIM, SKIP>::kBlock;
 
@@ -444,6 +464,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   // fixed-point window sized for any particle (|v| < c) would round a
   // thermal-scale contribution to a thousandth.
   constexpr bool kFix = !P::kAbs;
+  constexpr bool kConst = kFix || L <= 3;  // B-spline tables as compile-time constants
   // cell counts (the (l+3)^d cmax bound) only in 2D: a 3D tile holds fewer
   // particles than (l+3)^3 times its densest cell, so its bound is the tile's
   // particle count, and the LDS the counts would take buys 3D tiles room
@@ -543,14 +564,17 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   if (tid >= 6 && tid < 13) sred[tid] = 0;
   __syncthreads();
 
-  // 2D FP32: the leading coefficients of the T_l tables in vector registers,
-  // so that the first Horner step of each node reads one scalar operand (an
-  // instruction reads at most one) and needs no copy
+  // T_l with l + 1 nodes comes from its moments.  With l + 2 it comes from the
+  // run's tables, in 2D FP32 with their leading coefficients in vector
+  // registers, so that the first Horner step of each node reads one scalar
+  // operand (an instruction reads at most one) and needs no copy.
+  constexpr bool kMoments = KT == L + 1;
+  constexpr bool kTop = !kMoments && kFix && DIM == 2;
   Real ttop[2][KT];
 #pragma unroll
   for (int d = 0; d < 2; ++d)
 #pragma unroll
-    for (int k = 0; k < KT; ++k) ttop[d][k] = (kFix && DIM == 2) ? in_vgpr(float(R.T[d].c[k][L])) : Real(0);
+    for (int k = 0; k < KT; ++k) ttop[d][k] = kTop ? in_vgpr(float(R.T[d].c[k][L])) : Real(0);
 
   // the tile's particles, from its first one (offsets from part_off)
   PBuf<Real> B = A.buf[A.st->parity];
@@ -582,9 +606,9 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     nn[d] = pin(n);
     rlo[d] = pin(max(fo[d] - R.glo[d], jo[d] - R.dlo[d]));
     rhi[d] = pin(min(fo[d] + fs[d] - 1 - R.ghi[d], jo[d] + jsz[d] - 1 - R.dhi[d]));
-    hoff[d] = pin(R.Wh[d].first - fo[d]);
-    toff[d] = pin(R.T[d].first - fo[d]);
-    uoff[d] = pin(R.Wi[d].first - jo[d]);
+    hoff[d] = pin(kWh.first - fo[d]);
+    toff[d] = pin(R.tf[d].first - fo[d]);
+    uoff[d] = pin(kWi.first - jo[d]);
     jo_[d] = pin(jo[d]);
   }
   // offset along axis d in the current and count windows (their row and
@@ -746,23 +770,24 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     // ---- weights at x^n --------------------------------------------------
     Real wh[3][NW], wt[3][KT];
     int ih[3] = {0, 0, 0}, it[3] = {0, 0, 0};
-    // FP32 evaluates the B-spline tables from literal constants; FP64 loads
-    // them (64-bit literals would each take registers)
+    // the quartic tables are literal constants in FP32 and loaded in FP64
+    // (64-bit literals would each take registers)
     auto weights_h = [&](int d, const Tab<Real>& Th) {
       int b;
       Real gg;
       tab_split(Th, c[d], f[d], b, gg);
-      wtab_eval<L, NW, kFix>(Th, gg, wh[d]);
+      wtab_eval<L, NW>(Th, gg, wh[d]);
       ih[d] = rel[d] + (b - c[d]) + hoff[d];
     };
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-      if constexpr (kFix) weights_h(d, kWh);
+      if constexpr (kConst) weights_h(d, kWh);
       else weights_h(d, R.Wh[d]);
       int b;
       Real gg;
-      split_rt(R.T[d], c[d], f[d], b, gg);
-      tab_eval<L, KT, true>(R.T[d], gg, wt[d], (kFix && DIM == 2) ? ttop[d] : nullptr);
+      split_rt(R.tf[d].sigma, c[d], f[d], b, gg);
+      if constexpr (kMoments) tfac_eval<L>(R.tf[d], gg, wt[d]);
+      else tab_eval<L, KT, true>(R.T[d], gg, wt[d], kTop ? ttop[d] : nullptr);
       it[d] = rel[d] + (b - c[d]) + toff[d];
     }
 
@@ -882,7 +907,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
       tab_split(Tw, c[d], f[d], b0, g0);
       tab_split(Tw, cn[d], fn[d], b1, g1);
       Real s0[NW], s1[NW], dA[NW], dB[NW], a0[NU], ds[NU];
-      wtab_eval<L, NW, kFix>(Tw, g0, s0);
+      wtab_eval<L, NW>(Tw, g0, s0);
       const int db = b1 - b0;
       cross[d] = db != 0;
       const bool shA = db < 0, shB = db > 0;
@@ -893,7 +918,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
       if (__all(fabs(dd[d]) >= Real(0.0625))) {
         // every step of the wave is long: S1 - S0 directly keeps its
         // precision (rounding of order one against |step| >= 1/16)
-        wtab_eval<L, NW, kFix>(Tw, g1, s1);
+        wtab_eval<L, NW>(Tw, g1, s1);
 #pragma unroll
         for (int k = 0; k < NU; ++k) {
           a0[k] = shA ? (k >= 1 ? s0[k - 1] : Real(0)) : (k < NW ? s0[k] : Real(0));
@@ -902,7 +927,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
         }
       } else if (!__any(db != 0)) {
         // no lane of the wave changed its stencil: one divided difference
-        wtab_diff<L, kFix>(Tw, g0, g1, dd[d], dA);
+        wtab_diff<L, kConst>(Tw, g0, g1, dd[d], dA);
 #pragma unroll
         for (int k = 0; k < NU; ++k) {
           a0[k] = k < NW ? s0[k] : Real(0);
@@ -913,11 +938,11 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
         // it crossed (an end of g's range)
         const Real eA = (db == 0) ? g1 : (db > 0 ? Real(1) : Real(0));
         const Real lA = (db == 0) ? dd[d] : (db > 0 ? Real(1) - g0 : -g0);
-        wtab_diff<L, kFix>(Tw, g0, eA, lA, dA);
+        wtab_diff<L, kConst>(Tw, g0, eA, lA, dA);
         if (db != 0) {
           const Real sBv = (db > 0) ? Real(0) : Real(1);
           const Real lB = (db > 0) ? g1 : g1 - Real(1);
-          wtab_diff<L, kFix>(Tw, sBv, g1, lB, dB);
+          wtab_diff<L, kConst>(Tw, sBv, g1, lB, dB);
         } else {
 #pragma unroll
           for (int k = 0; k < NW; ++k) dB[k] = Real(0);
@@ -938,7 +963,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     };
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-      if constexpr (kFix) form_factors(d, kWi);
+      if constexpr (kConst) form_factors(d, kWi);
       else form_factors(d, R.Wi[d]);
     }
 

@@ -361,6 +361,8 @@ pic_status build_runs(pic_ctx* c, std::vector<RunDev<Real>>& out) {
       convert_table(wh, R.Wh[k]);
       convert_table(wi, R.Wi[k]);
       convert_table(tt, R.T[k]);
+      const TFac<double> tf = make_tfac(l, d.scheme == PIC_WT ? a : 0.5, tt);
+      R.tf[k] = {Real(tf.sigma), Real(tf.kappa), Real(tf.beta), Real(tf.u0), Real(tf.var), tf.first};
       int lo1, hi1, lo2, hi2, lo3, hi3;
       table_reach(wh, l + 1, lo1, hi1);
       table_reach(tt, KT, lo2, hi2);

@@ -137,4 +137,18 @@ bool build_table(int l, int kind, double a_in, Tab<double>& out, const char** er
   return true;
 }
 
+TFac<double> make_tfac(int l, double a, const Tab<double>& t) {
+  long double fact = 1.0L;
+  for (int i = 2; i <= l; ++i) fact *= i;
+  TFac<double> f;
+  f.sigma = t.sigma;
+  f.kappa = (double)(1.0L - 2.0L * a);
+  f.beta = (double)(1.0L / (2.0L * a * fact));
+  // node k lies at first + k from the split's base, the particle at sigma + g
+  f.u0 = (double)(frac(0.5L * l + (long double)a) - t.first - 1);
+  f.var = (double)(l / 12.0L + (long double)a * a / 3.0L);
+  f.first = t.first;
+  return f;
+}
+
 }  // namespace wtpic
