@@ -111,7 +111,8 @@ struct RunDev {
   Tab<Real> T[3];     // T_l (WT) or W_l (MC) on the integer lattice
 };
 
-// One of the two particle stores.
+// One of the two particle stores: the first holds the current particles, the
+// sort passes them through the second.
 template <class Real>
 struct PBuf {
   int* cell;      // packed cell (F32 layout only)
@@ -124,9 +125,7 @@ constexpr int kSpeciesShift = 30;
 
 // Device-side mutable state of a context.
 struct DevState {
-  int parity;                  // current particle store
   int sort_request;            // set when a tile's particles outgrew the staging margin
-  int pad0;
   int tile_queue;              // next tile for the persistent particle kernel
   unsigned long long n_nonfinite;
   unsigned long long n_out_of_range;
@@ -138,10 +137,17 @@ struct DevState {
   unsigned int pad1;
 };
 
+// What a launch or a sort leaves for a tile's next step.
+struct TileState {
+  int bb[6];       // box of the particles' cells: lo0, hi0, lo1, hi1, lo2, hi2
+  float jb[4];     // bounds of the current contributions, largest cell count
+  int seg[3];      // first electron, first positron, end
+};
+
 template <class Real>
 struct GpdArgs {
   const RunDev<Real>* runs;
-  const int* tile_run;   // run of each global tile
+  const int4* tiles;     // per tile: first cell (x, y, z) and run
   const int* seg;        // 2G+1 segment offsets: key 2g+s covers [seg[key], seg[key+1])
   int* bbox;             // per tile: lo0, hi0, lo1, hi1, lo2, hi2 (cells, tile-relative)
   float* jb;             // per tile: bounds of the current contributions and cell counts (gpd.hip)

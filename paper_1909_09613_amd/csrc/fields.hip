@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(256) diag_particles_kernel(DiagArgs<typename P
   using Real = typename P::Real;
   __shared__ double sh[16];
   const RunDev<Real>& R = A.runs[A.run];
-  const PBuf<Real> B = A.buf[A.st->parity];
+  const PBuf<Real> B = A.buf[0];
   double s[5] = {0, 0, 0, 0, 0};
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += stride) {
@@ -313,7 +313,7 @@ template <class P, int L, int DIM>
 __global__ void diag_rho_kernel(DiagArgs<typename P::Real> A, long long p0, long long np) {
   using Real = typename P::Real;
   const RunDev<Real>& R = A.runs[A.run];
-  const PBuf<Real> B = A.buf[A.st->parity];
+  const PBuf<Real> B = A.buf[0];
   const long long stride = (long long)gridDim.x * blockDim.x;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < np; i += stride) {
     const long long p = p0 + i;

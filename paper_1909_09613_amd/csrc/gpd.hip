@@ -249,6 +249,71 @@ __device__ __forceinline__ unsigned fresh_off(unsigned o) {
 // reduced to [0, n), differ by less than n.
 __device__ __forceinline__ int wrap_once(int m, int n) { return m + (n & (m >> 31)); }
 
+// m mod n for any m, by subtraction: a tile's windows start within a few
+// periods of [0, n), nearly always in it (an integer division takes some
+// forty instructions).
+__device__ __forceinline__ int wrap_sub(int m, int n) {
+  while (m < 0) m += n;
+  while (m >= n) m -= n;
+  return m;
+}
+
+// Reduction over a wave with DPP moves (row shifts, then the rows' last lanes
+// broadcast to the next rows): one vector instruction per step, where a
+// shuffle is a round trip through the LDS.  Lane 63 holds the result.
+template <int CTRL, int ROWS, class Op>
+__device__ __forceinline__ int dpp_step(int x, int ident, Op op) {
+  return op(x, __builtin_amdgcn_update_dpp(ident, x, CTRL, ROWS, 0xf, false));
+}
+template <class Op>
+__device__ __forceinline__ int wave_reduce(int x, int ident, Op op) {
+  x = dpp_step<0x111, 0xf>(x, ident, op);  // row_shr:1, 2, 4, 8
+  x = dpp_step<0x112, 0xf>(x, ident, op);
+  x = dpp_step<0x114, 0xf>(x, ident, op);
+  x = dpp_step<0x118, 0xf>(x, ident, op);
+  x = dpp_step<0x142, 0xa>(x, ident, op);  // row_bcast:15 into rows 1 and 3
+  x = dpp_step<0x143, 0xc>(x, ident, op);  // row_bcast:31 into rows 2 and 3
+  return x;
+}
+__device__ __forceinline__ int wave_min(int x) {
+  return wave_reduce(x, INT_MAX, [](int a, int b) { return min(a, b); });
+}
+__device__ __forceinline__ int wave_max(int x) {
+  return wave_reduce(x, INT_MIN, [](int a, int b) { return max(a, b); });
+}
+__device__ __forceinline__ int wave_sum(int x) {
+  return wave_reduce(x, 0, [](int a, int b) { return a + b; });
+}
+
+// Nodes of a box of sz[0] x sz[1] (x sz[2]) by their number, without integer
+// divisions (some forty instructions each): the product with an approximate
+// reciprocal, a half step away from the integers, which the approximation
+// cannot cross while the numbers stay far below 2^20.
+template <int DIM>
+struct BoxNodes {
+  int n, s0, s1;
+  float inv0, inv1;
+  __device__ __forceinline__ explicit BoxNodes(const int sz[3])
+      : n(sz[0] * sz[1] * (DIM == 3 ? sz[2] : 1)), s0(sz[0]), s1(sz[1]),
+        inv0(__builtin_amdgcn_rcpf((float)sz[0])), inv1(__builtin_amdgcn_rcpf((float)sz[1])) {}
+  __device__ __forceinline__ void at(int i, int& x, int& y, int& z) const {
+    const int q = (int)(((float)i + 0.5f) * inv0);
+    x = i - imul24(q, s0);
+    z = DIM == 3 ? (int)(((float)q + 0.5f) * inv1) : 0;
+    y = DIM == 3 ? q - imul24(z, s1) : q;
+  }
+};
+
+// A window position x >= 0 cells past a canonical cell g0, on the axis's n
+// cells: one subtraction unless the window is wider than the axis.
+__device__ __forceinline__ int wrap_window(int m, int n) {
+  if (m >= n) {
+    m -= n;
+    if (m >= n) m %= n;
+  }
+  return m;
+}
+
 // 1 / sqrt(x) and 1 / x for x >= 1 (1 + |u|^2, 1 + |t|^2).  FP32: the
 // hardware approximations (1 ulp).  FP64: the hardware estimates (about 23
 // correct bits) refined by two Newton steps, each of which doubles the
@@ -352,10 +417,9 @@ struct GpdShape {
 };
 
 template <class P, int L, int DIM, int KT, bool SKIP, int CP>
-__device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
-                                         const RunDev<typename P::Real>* __restrict__ runs,
-                                         const int* __restrict__ tile_run, const int g,
-                                         unsigned char* lds, int* sred, typename P::Real* spc) {
+__device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, const RunDev<typename P::Real>& R,
+                                         const int4 where, const TileState ts, const int g, unsigned char* lds,
+                                         int* sred, typename P::Real* spc) {
   using Real = typename P::Real;
   using Acc = typename P::Acc;
   using Real2 = typename Pair<Real>::T;
@@ -368,17 +432,8 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   const int tid = threadIdx.x;
   const int nth = GpdShape<L, DIM, SKIP>::kBlock;
 
-  const int r = tile_run[g];
-  const RunDev<Real>& R = runs[r];
-  const int lt = g - R.tile0;
-  int org[3];
-  org[0] = (lt % R.ntile[0]) * A.tile[0];
-  org[1] = ((lt / R.ntile[0]) % R.ntile[1]) * A.tile[1];
-  org[2] = (DIM == 3) ? (lt / (R.ntile[0] * R.ntile[1])) * A.tile[2] : 0;
-
-  int bb[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) bb[i] = A.bbox[g * 6 + i];
+  const int org[3] = {where.x, where.y, where.z};
+  const int* bb = ts.bb;
   int fo[3] = {0, 0, 0}, fs[3] = {1, 1, 1}, jo[3] = {0, 0, 0}, jsz[3] = {1, 1, 1};
   bool fits = true;
 #pragma unroll
@@ -389,7 +444,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     jsz[d] = bb[2 * d + 1] + R.dhi[d] - jo[d] + 1;
     fits = fits && fs[d] >= 1 && jsz[d] >= 1 && fs[d] <= A.fw[d] && jsz[d] <= A.jw[d];
   }
-  const int sA = A.seg[2 * g], sB = A.seg[2 * g + 1], sC = A.seg[2 * g + 2];
+  const int sA = ts.seg[0], sB = ts.seg[1], sC = ts.seg[2];
   // byte offsets within the tile are 32-bit
   fits = fits && (unsigned)(sC - sA) <= 0xffffffffu / (unsigned)sizeof(Real);
   if (!fits) {
@@ -482,14 +537,14 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   if (kFix) {
     int reach = 1;
     for (int d = 0; d < DIM; ++d) reach *= L + 3;
-    const double nmax = fmin((double)(sC - sA), (double)reach * (double)A.jb[4 * g + 3]);
+    const double nmax = fmin((double)(sC - sA), (double)reach * (double)ts.jb[3]);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      thr[c] = Real(2) * Real(A.jb[4 * g + c]);
+      thr[c] = Real(2) * Real(ts.jb[c]);
       const double jm = fmax(fabs(R.js[0][c]), fabs(R.js[1][c]));
       const double bnd = nmax * jm * (double)thr[c];
       if (bnd > 0.0) {
-        qd[c] = bnd / 2145386496.0;  // 2^31 (1 - 2^-10): room for rounding
+        qd[c] = bnd * (1.0 / 2145386496.0);  // 2^31 (1 - 2^-10): room for rounding
         qinv[c] = Real(1.0 / qd[c]);
       }
     }
@@ -529,30 +584,47 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   int* Cw = Qf + 6 * jcap;
 
   // ---- stage E, B on the window; clear the current tile ------------------
-  const int nfs = (smode == 1) ? 0 : fs[0] * fs[1] * fs[2];
-  for (int i = tid; i < nfs; i += nth) {
-    const int w0 = i % fs[0];
-    const int q = i / fs[0];
-    const int w1 = q % fs[1];
-    const int w2 = q / fs[1];
-    const int gx = wrapi(org[0] + fo[0] + w0, R.n[0]);
-    const int gy = wrapi(org[1] + fo[1] + w1, R.n[1]);
-    const int gz = (DIM == 3) ? wrapi(org[2] + fo[2] + w2, R.n[2]) : 0;
-    const long long gi = gx + (long long)R.n[0] * (gy + (long long)R.n[1] * gz);
-    const int li = w0 + fpx * w1 + fpz * w2;
-    if (DIM == 2) {
-      Real2 a, b;
-      a.x = Fg[0 * NT + gi];
-      a.y = Fg[4 * NT + gi];
-      b.x = Fg[1 * NT + gi];
-      b.y = Fg[3 * NT + gi];
-      P1[li] = a;
-      P2[li] = b;
-      P3[li] = Fg[2 * NT + gi];
-      P4[li] = Fg[5 * NT + gi];
-    } else {
+  // the box's first node on the grid; a window's nodes follow it
+  int fg[3] = {0, 0, 0}, jg[3] = {0, 0, 0};
 #pragma unroll
-      for (int c = 0; c < 6; ++c) F6[c * fcap + li] = Fg[c * NT + gi];
+  for (int d = 0; d < DIM; ++d) {
+    fg[d] = wrap_sub(org[d] + fo[d], R.n[d]);
+    jg[d] = wrap_sub(org[d] + jo[d], R.n[d]);
+  }
+  auto node = [&](const int* g0, int x, int y, int z) {
+    const int gx = wrap_window(g0[0] + x, R.n[0]), gy = wrap_window(g0[1] + y, R.n[1]);
+    const int gz = (DIM == 3) ? wrap_window(g0[2] + z, R.n[2]) : 0;
+    return gx + R.n[0] * (gy + R.n[1] * gz);  // a run has fewer than 2^30 cells
+  };
+  if (smode != 1) {
+    // two nodes per thread and pass, with the loads of both in flight (a pass
+    // waits for memory once)
+    const BoxNodes<DIM> box(fs);
+    for (int i0 = tid; i0 < box.n; i0 += 2 * nth) {
+      Real v[2][6];
+      int li[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        // (past the end: the last node once more, with the same values)
+        int x, y, z;
+        box.at(min(i0 + k * nth, box.n - 1), x, y, z);
+        const Real* q = Fg + node(fg, x, y, z);
+        li[k] = x + imul24(fpx, y) + (DIM == 3 ? imul24(fpz, z) : 0);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) v[k][c] = q[c * NT];
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (DIM == 2) {
+          P1[li[k]] = Real2{v[k][0], v[k][4]};
+          P2[li[k]] = Real2{v[k][1], v[k][3]};
+          P3[li[k]] = v[k][2];
+          P4[li[k]] = v[k][5];
+        } else {
+#pragma unroll
+          for (int c = 0; c < 6; ++c) F6[c * fcap + li[k]] = v[k][c];
+        }
+      }
     }
   }
   if (kFix) {
@@ -577,7 +649,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     for (int k = 0; k < KT; ++k) ttop[d][k] = kTop ? in_vgpr(float(R.T[d].c[k][L])) : Real(0);
 
   // the tile's particles, from its first one (offsets from part_off)
-  PBuf<Real> B = A.buf[A.st->parity];
+  PBuf<Real> B = A.buf[0];
   B.cell += sA;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
@@ -601,7 +673,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     const int n = R.n[d];
     const int slack = max(0, n - 1 - (bb[2 * d + 1] - bb[2 * d]));
     const int lo = bb[2 * d] - (slack >> 1);
-    co[d] = pin(wrapi(org[d] + lo, n));
+    co[d] = pin(wrap_sub(org[d] + lo, n));
     lo_[d] = pin(lo);
     nn[d] = pin(n);
     rlo[d] = pin(max(fo[d] - R.glo[d], jo[d] - R.dlo[d]));
@@ -1150,29 +1222,28 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   // ---- box and counters: wave reduction, then one LDS atomic per wave ------
 #pragma unroll
   for (int d = 0; d < DIM; ++d) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      bmin[d] = min(bmin[d], __shfl_xor(bmin[d], off));
-      bmax[d] = max(bmax[d], __shfl_xor(bmax[d], off));
-    }
+    bmin[d] = wave_min(bmin[d]);
+    bmax[d] = wave_max(bmax[d]);
   }
+  if (kFix) {
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    nbad += __shfl_xor(nbad, off);
-    noor += __shfl_xor(noor, off);
-    if (kFix) {
-#pragma unroll
-      for (int c = 0; c < 3; ++c) mnew[c] = max(mnew[c], __shfl_xor(mnew[c], off));
-    }
+    for (int c = 0; c < 3; ++c) mnew[c] = wave_max(mnew[c]);
   }
-  if ((tid & 63) == 0) {
+  const bool faults = __any(nbad | noor);
+  if (faults) {
+    nbad = wave_sum(nbad);
+    noor = wave_sum(noor);
+  }
+  if ((tid & 63) == 63) {
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
       atomicMin(&sred[2 * d], bmin[d]);
       atomicMax(&sred[2 * d + 1], bmax[d]);
     }
-    if (nbad) atomicAdd(&sred[6], nbad);
-    if (noor) atomicAdd(&sred[7], noor);
+    if (faults) {
+      atomicAdd(&sred[6], nbad);
+      atomicAdd(&sred[7], noor);
+    }
     if (kFix) {
 #pragma unroll
       for (int c = 0; c < 3; ++c) atomicMax(&sred[8 + c], mnew[c]);
@@ -1184,41 +1255,37 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
     // left in place by a non-finite push are counted at their cell)
     int cm = 0;
     for (int i = tid; i < jcap; i += nth) cm = max(cm, Cw[i]);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) cm = max(cm, __shfl_xor(cm, off));
-    if ((tid & 63) == 0) atomicMax(&sred[11], cm);
+    cm = wave_max(cm);
+    if ((tid & 63) == 63) atomicMax(&sred[11], cm);
   }
 
   // ---- flush the current tile ------------------------------------------------
   double* Jg = A.J + R.cell0;
   [[maybe_unused]] const bool coarse_used = kGlobCoarse && sred[12] != 0;
-  const int njs = (smode == 1) ? 0 : jsz[0] * jsz[1] * jsz[2];
-  for (int i = tid; i < njs; i += nth) {
-    const int w0 = i % jsz[0];
-    const int q = i / jsz[0];
-    const int w1 = q % jsz[1];
-    const int w2 = q / jsz[1];
-    const int gx = wrapi(org[0] + jo[0] + w0, R.n[0]);
-    const int gy = wrapi(org[1] + jo[1] + w1, R.n[1]);
-    const int gz = (DIM == 3) ? wrapi(org[2] + jo[2] + w2, R.n[2]) : 0;
-    const long long gi = gx + (long long)R.n[0] * (gy + (long long)R.n[1] * gz);
-    const int li = w0 + jpx * w1 + jpz * w2;
+  if (smode != 1) {
+    const BoxNodes<DIM> box(jsz);
+    for (int i = tid; i < box.n; i += nth) {
+      int x, y, z;
+      box.at(i, x, y, z);
+      double* o = Jg + node(jg, x, y, z);
+      const int li = x + imul24(jpx, y) + (DIM == 3 ? imul24(jpz, z) : 0);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      double v;
-      if constexpr (kGlobCoarse) {
-        v = (double)Qf[c * jcap + li] * qd[c];
-        if (coarse_used) {
-          // the coarse sums were added at the L2; read them there and leave
-          // the window zero for the group's next tile
-          float* q = Qc + c * jcap + li;
-          v += (double)__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          __hip_atomic_store(q, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int c = 0; c < 3; ++c) {
+        double v;
+        if constexpr (kGlobCoarse) {
+          v = (double)Qf[c * jcap + li] * qd[c];
+          if (coarse_used) {
+            // the coarse sums were added at the L2; read them there and leave
+            // the window zero for the group's next tile
+            float* q = Qc + c * jcap + li;
+            v += (double)__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(q, 0.0f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        } else {
+          v = kFix ? (double)Qf[c * jcap + li] * qd[c] + (double)Qc[c * jcap + li] : (double)Jl[c * jcap + li];
         }
-      } else {
-        v = kFix ? (double)Qf[c * jcap + li] * qd[c] + (double)Qc[c * jcap + li] : (double)Jl[c * jcap + li];
+        if (v != 0.0) unsafeAtomicAdd(o + c * NT, v);
       }
-      if (v != 0.0) unsafeAtomicAdd(Jg + c * NT + gi, v);
     }
   }
   if (kGlobCoarse && coarse_used) __threadfence();  // the clears land before the next tile's adds
@@ -1255,45 +1322,72 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A,
   }
 }
 
-// Persistent workgroups: each takes tiles from a device queue until none are
-// left, so uneven tiles (edge tiles, runs of different size) balance.  The
-// queue starts at zero (set at initialisation, then rewound by the last
-// group of every launch).  Waves per SIMD and group size as GpdShape gives:
-// where the kernel is held to four waves per SIMD (two 512-thread groups per
-// CU, at most 128 registers), a fifth register block would drop a wave and
-// halve the groups a CU holds, which costs far more than a few spilled
-// values (3D, l = 2: 2.90 ms against 3.10 ms for three 256-thread groups of
-// 156 registers at 256x128x128).
+// What the previous launch or sort left for a tile, one value per lane of one
+// load, as wave-uniform values: the box, the bounds of the current and the
+// segments of its particles.
+template <class Real>
+__device__ __forceinline__ TileState load_tile(const GpdArgs<Real>& A, int g) {
+  const int lane = min((int)(threadIdx.x & 63), 12);
+  const int* p = lane < 6 ? A.bbox + g * 6 + lane
+                          : (lane < 10 ? reinterpret_cast<const int*>(A.jb) + 4 * g + (lane - 6)
+                                       : A.seg + 2 * g + (lane - 10));
+  const int v = *p;
+  TileState t;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) t.bb[i] = __builtin_amdgcn_readlane(v, i);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) t.jb[i] = __int_as_float(__builtin_amdgcn_readlane(v, 6 + i));
+#pragma unroll
+  for (int i = 0; i < 3; ++i) t.seg[i] = __builtin_amdgcn_readlane(v, 10 + i);
+  return t;
+}
+
+// Persistent workgroups: the first tile of a group is its own number, further
+// ones come from a device queue until none are left, so uneven tiles (edge
+// tiles, runs of different size) balance; a launch with a group per tile takes
+// no tickets at all.  The queue starts at zero (set at initialisation, then
+// rewound by the last group of every launch).  Waves per SIMD and group size
+// as GpdShape gives: where the kernel is held to four waves per SIMD (two
+// 512-thread groups per CU, at most 128 registers), a fifth register block
+// would drop a wave and halve the groups a CU holds, which costs far more than
+// a few spilled values (3D, l = 2: 2.90 ms against 3.10 ms for three
+// 256-thread groups of 156 registers at 256x128x128).
 template <class P, int L, int DIM, bool SKIP, int CP>
 __global__ void __launch_bounds__((GpdShape<L, DIM, SKIP>::kBlock))
 __attribute__((amdgpu_waves_per_eu(GpdShape<L, DIM, SKIP>::kWaves)))
     gpd_kernel(GpdArgs<typename P::Real> A, const RunDev<typename P::Real>* __restrict__ runs,
-               const int* __restrict__ tile_run) {
+               const int4* __restrict__ tiles) {
   extern __shared__ __align__(16) unsigned char lds_dyn[];
   __shared__ int sred[13];
   __shared__ int next;
   __shared__ __align__(32) typename P::Real spc[8];   // per-species constants of the tile's run
-  for (;;) {
-    if (threadIdx.x == 0) next = atomicAdd(&A.st->tile_queue, 1);
-    __syncthreads();
-    const int g = next;
-    __syncthreads();
-    if (g >= A.G) {
-      // the last group to find the queue empty rewinds it for the next
-      // launch (every group has taken its final ticket by then)
-      if (threadIdx.x == 0 && atomicAdd(&A.st->groups_done, 1u) == gridDim.x - 1) {
-        A.st->tile_queue = 0;
-        A.st->groups_done = 0;
-        A.st->gpd_launches += 1;
-      }
-      return;
-    }
-    const int kt = runs[tile_run[g]].KT;
-    if (kt == L + 1)
-      gpd_tile<P, L, DIM, L + 1, SKIP, CP>(A, runs, tile_run, g, lds_dyn, sred, spc);
+  const bool queue = A.G > (int)gridDim.x;
+  for (int g = blockIdx.x; g < A.G;) {
+    const int4 where = tiles[g];
+    const TileState ts = load_tile(A, g);
+    const RunDev<typename P::Real>& R = runs[where.w];
+    if (R.KT == L + 1)
+      gpd_tile<P, L, DIM, L + 1, SKIP, CP>(A, R, where, ts, g, lds_dyn, sred, spc);
     else
-      gpd_tile<P, L, DIM, L + 2, SKIP, CP>(A, runs, tile_run, g, lds_dyn, sred, spc);
+      gpd_tile<P, L, DIM, L + 2, SKIP, CP>(A, R, where, ts, g, lds_dyn, sred, spc);
+    if (!queue) break;
     __syncthreads();
+    if (threadIdx.x == 0) next = (int)gridDim.x + atomicAdd(&A.st->tile_queue, 1);
+    __syncthreads();
+    g = next;
+  }
+  if (threadIdx.x != 0) return;
+  if (SKIP || queue) {
+    // the last group to find the queue empty rewinds it for the next launch
+    // (every group has taken its final ticket by then) and counts the
+    // launch, which the skip variant's groups read as the time
+    if (atomicAdd(&A.st->groups_done, 1u) == gridDim.x - 1) {
+      A.st->tile_queue = 0;
+      A.st->groups_done = 0;
+      A.st->gpd_launches += 1;
+    }
+  } else if (blockIdx.x == 0) {
+    A.st->gpd_launches += 1;
   }
 }
 
@@ -1307,8 +1401,7 @@ static hipError_t launch_variant(const GpdArgs<typename P::Real>& a, size_t lds,
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL((gpd_kernel<P, L, DIM, SKIP, CP>), dim3(grid), dim3(GpdShape<L, DIM, SKIP>::kBlock), lds, s,
-                     a, a.runs,
-                     a.tile_run);
+                     a, a.runs, a.tiles);
   return hipGetLastError();
 }
 
@@ -1343,7 +1436,7 @@ __global__ void __launch_bounds__(256) rho_tiles_kernel(GpdArgs<typename P::Real
   const int ntiles = R.ntile[0] * R.ntile[1] * R.ntile[2];
   const int jwx = A.jw[0], jwy = A.jw[1];
   const int jcap = jwx * jwy * (DIM == 3 ? A.jw[2] : 1);
-  const PBuf<Real> B = A.buf[A.st->parity];
+  const PBuf<Real> B = A.buf[0];
   const int tid = threadIdx.x;
   const double qv[2] = {R.Q[0] / R.Vc, R.Q[1] / R.Vc};
   for (int lt = blockIdx.x; lt < ntiles; lt += gridDim.x) {

@@ -59,7 +59,7 @@ struct Layout {
   size_t p_cell[2], p_pos[2][3], p_u[2][3], p_tag[2];
   // fields / current: component-major
   // scratch
-  size_t s_state, s_runs, s_tile_run, s_counts, s_cursor, s_seg, s_bbox, s_jb, s_keys, s_blk_run, s_blk_first, s_acc,
+  size_t s_state, s_runs, s_tile_run, s_tiles, s_counts, s_cursor, s_seg, s_bbox, s_jb, s_keys, s_blk_run, s_blk_first, s_acc,
       s_part, s_rho, s_coarse;
   size_t coarse_bytes;
   long long gmax;
@@ -175,6 +175,8 @@ Layout make_layout(const pic_run_desc* runs, int n_runs) {
   off += align_up((f64 ? sizeof(RunDev<double>) : sizeof(RunDev<float>)) * n_runs);
   L.s_tile_run = off;
   off += align_up(4 * gmax);
+  L.s_tiles = off;
+  off += align_up(sizeof(int4) * gmax);
   L.s_counts = off;
   off += align_up(4 * 2 * gmax);
   L.s_cursor = off;
@@ -245,6 +247,7 @@ struct pic_ctx {
   hipGraphExec_t gexec_gpd = nullptr;
   hipGraph_t graph_gpd = nullptr;
   std::vector<int> tile_run_host;
+  std::vector<int4> tiles_host;
   std::vector<int> blk_run_host, blk_first_host;
   // called by pic_destroy once the stream has drained (allocation-free
   // initialisation: releases the device's static scratch)
@@ -478,12 +481,21 @@ pic_status apply_tiling(pic_ctx* c) {
   }
   // device tables
   c->tile_run_host.assign(G, 0);
-  for (int r = 0; r < c->nruns; ++r)
-    for (int t = 0; t < c->runs[r].ntiles; ++t) c->tile_run_host[c->runs[r].tile0 + t] = r;
+  c->tiles_host.assign(G, int4{0, 0, 0, 0});
+  for (int r = 0; r < c->nruns; ++r) {
+    const RunHost& H = c->runs[r];
+    for (int t = 0; t < H.ntiles; ++t) {
+      c->tile_run_host[H.tile0 + t] = r;
+      c->tiles_host[H.tile0 + t] = {t % H.ntile[0] * c->tile[0], t / H.ntile[0] % H.ntile[1] * c->tile[1],
+                                    nd == 3 ? t / (H.ntile[0] * H.ntile[1]) * c->tile[2] : 0, r};
+    }
+  }
   hipError_t e = host_copy(c, c->S + c->lay.s_runs, rd.data(), sizeof(RunDev<Real>) * rd.size(),
                                 hipMemcpyHostToDevice);
   if (e == hipSuccess)
     e = host_copy(c, c->S + c->lay.s_tile_run, c->tile_run_host.data(), 4 * G, hipMemcpyHostToDevice);
+  if (e == hipSuccess)
+    e = host_copy(c, c->S + c->lay.s_tiles, c->tiles_host.data(), sizeof(int4) * G, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   return c->hip(e, "apply_tiling");
 }
@@ -519,7 +531,7 @@ template <class Real>
 GpdArgs<Real> gpd_args(pic_ctx* c) {
   GpdArgs<Real> a{};
   a.runs = reinterpret_cast<const RunDev<Real>*>(c->S + c->lay.s_runs);
-  a.tile_run = reinterpret_cast<const int*>(c->S + c->lay.s_tile_run);
+  a.tiles = reinterpret_cast<const int4*>(c->S + c->lay.s_tiles);
   a.seg = reinterpret_cast<const int*>(c->S + c->lay.s_seg);
   a.bbox = reinterpret_cast<int*>(c->S + c->lay.s_bbox);
   a.jb = reinterpret_cast<float*>(c->S + c->lay.s_jb);
@@ -663,14 +675,6 @@ pic_status do_gpd(pic_ctx* c, bool capture) {
 
 pic_status do_fields(pic_ctx* c) { return c->f64() ? enqueue_fields<double>(c) : enqueue_fields<float>(c); }
 
-int read_parity(pic_ctx* c, pic_status* st) {
-  DevState ds{};
-  hipError_t e = host_copy(c, &ds, c->state(), sizeof ds, hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  *st = c->hip(e, "read state");
-  return ds.parity;
-}
-
 // Autotuner candidates: tile (cells), staging margin, sort cadence; the first
 // of each list is the default tiling of pic_init.
 struct Cand {
@@ -713,9 +717,6 @@ template <class Real>
 pic_status set_particles_t(pic_ctx* c, int run, int species, const double* x, const double* u,
                                   int64_t n) {
   RunHost& H = c->runs[run];
-  pic_status st;
-  const int par = read_parity(c, &st);
-  if (st != PIC_OK) return st;
   if (c->sorted_once) {
     // sorted stores interleave the species: the whole run must be re-set
     H.set[0] = H.set[1] = false;
@@ -759,13 +760,13 @@ pic_status set_particles_t(pic_ctx* c, int run, int species, const double* x, co
   }
   const size_t rs = sizeof(Real);
   hipError_t e = hipSuccess;
-  if (!c->f64()) e = host_copy(c, c->P + c->lay.p_cell[par] + 4 * base, cell.data(), 4 * n, hipMemcpyHostToDevice);
+  if (!c->f64()) e = host_copy(c, c->P + c->lay.p_cell[0] + 4 * base, cell.data(), 4 * n, hipMemcpyHostToDevice);
   for (int k = 0; k < c->ndim && e == hipSuccess; ++k)
-    e = host_copy(c, c->P + c->lay.p_pos[par][k] + rs * base, pos[k].data(), rs * n, hipMemcpyHostToDevice);
+    e = host_copy(c, c->P + c->lay.p_pos[0][k] + rs * base, pos[k].data(), rs * n, hipMemcpyHostToDevice);
   for (int k = 0; k < 3 && e == hipSuccess; ++k)
-    e = host_copy(c, c->P + c->lay.p_u[par][k] + rs * base, uu[k].data(), rs * n, hipMemcpyHostToDevice);
+    e = host_copy(c, c->P + c->lay.p_u[0][k] + rs * base, uu[k].data(), rs * n, hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = host_copy(c, c->P + c->lay.p_tag[par] + 4 * base, tag.data(), 4 * n, hipMemcpyHostToDevice);
+    e = host_copy(c, c->P + c->lay.p_tag[0] + 4 * base, tag.data(), 4 * n, hipMemcpyHostToDevice);
   const int one = 1;
   if (e == hipSuccess)
     e = host_copy(c, &c->state()->sort_request, &one, sizeof one, hipMemcpyHostToDevice);
@@ -780,26 +781,23 @@ pic_status set_particles_t(pic_ctx* c, int run, int species, const double* x, co
 template <class Real>
 pic_status get_particles_t(pic_ctx* c, int run, int species, double* x, double* u, int64_t n) {
   const RunHost& H = c->runs[run];
-  pic_status st;
-  const int par = read_parity(c, &st);
-  if (st != PIC_OK) return st;
   const long long base = H.p0, cnt = 2 * H.nps;
   const size_t rs = sizeof(Real);
   std::vector<int> cell(c->f64() ? 0 : cnt), tag(cnt);
   std::vector<Real> pos[3], uu[3];
   hipError_t e = hipSuccess;
-  if (!c->f64()) e = host_copy(c, cell.data(), c->P + c->lay.p_cell[par] + 4 * base, 4 * cnt, hipMemcpyDeviceToHost);
+  if (!c->f64()) e = host_copy(c, cell.data(), c->P + c->lay.p_cell[0] + 4 * base, 4 * cnt, hipMemcpyDeviceToHost);
   for (int k = 0; k < 3; ++k) {
     uu[k].resize(cnt);
     if (e == hipSuccess)
-      e = host_copy(c, uu[k].data(), c->P + c->lay.p_u[par][k] + rs * base, rs * cnt, hipMemcpyDeviceToHost);
+      e = host_copy(c, uu[k].data(), c->P + c->lay.p_u[0][k] + rs * base, rs * cnt, hipMemcpyDeviceToHost);
     if (k < c->ndim) {
       pos[k].resize(cnt);
       if (e == hipSuccess)
-        e = host_copy(c, pos[k].data(), c->P + c->lay.p_pos[par][k] + rs * base, rs * cnt, hipMemcpyDeviceToHost);
+        e = host_copy(c, pos[k].data(), c->P + c->lay.p_pos[0][k] + rs * base, rs * cnt, hipMemcpyDeviceToHost);
     }
   }
-  if (e == hipSuccess) e = host_copy(c, tag.data(), c->P + c->lay.p_tag[par] + 4 * base, 4 * cnt, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = host_copy(c, tag.data(), c->P + c->lay.p_tag[0] + 4 * base, 4 * cnt, hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return c->hip(e, "get_particles");
   long long found = 0;
@@ -1246,10 +1244,7 @@ pic_status pic_autotune(pic_ctx* c, int32_t trial_steps, int32_t chosen[5], doub
 
   // snapshot: the current particle store (the other one is the sort's
   // destination and holds nothing yet), fields, current, device state
-  const int par = read_parity(c, &st);
-  if (st != PIC_OK) return st;
-  const size_t p_lo = c->lay.p_cell[par];
-  const size_t p_hi = par == 0 ? c->lay.p_cell[1] : c->lay.bytes[0];
+  const size_t p_lo = c->lay.p_cell[0], p_hi = c->lay.p_cell[1];
   std::vector<char> hp(p_hi - p_lo), hf(c->lay.bytes[1]), hj(c->lay.bytes[2]);
   DevState ds{};
   hipError_t e = host_copy(c, hp.data(), c->P + p_lo, hp.size(), hipMemcpyDeviceToHost);

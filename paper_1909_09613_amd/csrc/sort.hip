@@ -109,7 +109,7 @@ template <class P, int DIM>
 __global__ void sort_count(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
   if (!A.st->sort_request) return;
-  const PBuf<Real> B = A.buf[A.st->parity];
+  const PBuf<Real> B = A.buf[0];
   const long long stride = (long long)gridDim.x * blockDim.x;
   const long long start = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   // every lane of a wave iterates the same number of times (wave_add)
@@ -162,9 +162,8 @@ template <class P, int DIM>
 __global__ void sort_scatter(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
   if (!A.st->sort_request) return;
-  const int par = A.st->parity;
-  const PBuf<Real> S = A.buf[par];
-  const PBuf<Real> D = A.buf[par ^ 1];
+  const PBuf<Real> S = A.buf[0];
+  const PBuf<Real> D = A.buf[1];
   const long long stride = (long long)gridDim.x * blockDim.x;
   const long long start = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long nit = (A.np_total + stride - 1) / stride;
@@ -260,9 +259,8 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int nwave = kArrangeBlock / 64;
   constexpr int U = kArrangeItems, V = 4;
-  const int par = A.st->parity;
-  const PBuf<Real> S = A.buf[par ^ 1];
-  const PBuf<Real> D = A.buf[par];
+  const PBuf<Real> S = A.buf[1];
+  const PBuf<Real> D = A.buf[0];
   const unsigned long long below = (1ull << lane) - 1ull;
   // the scatter is done with the cursors: clear them for the next sort
   for (int i = blockIdx.x * kArrangeBlock + tid; i < A.nkeys; i += gridDim.x * kArrangeBlock) A.cursor[i] = 0;
