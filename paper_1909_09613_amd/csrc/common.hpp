@@ -60,8 +60,10 @@ __host__ __device__ inline void unpack_cell(int c, int& x, int& y, int& z) {
 //    falls on other banks than the rest of the half-wave's reads.  Current
 //    atomics showed no such dependence.
 //  - 3D FP32 (16 x 4 x 4 tiles, l <= 2, c dt <= dx/2): fields 21 x 9 nodes
-//    per plane at (21, 192), current 23 x 11 at (23, 256) (planes rounded up
-//    to a multiple of 8).
+//    per plane at (24, 216), current 23 x 11 at (24, 264): the LDS serves
+//    two rows of 16 cells at once, every second one (the sort's order), which
+//    at 2 x 24 elements fall on the two halves of the banks.  128x128x64 with
+//    that order: 719 us at (21, 192) and (23, 256), 682 us at these.
 // (The same for the FP64 kernel measured no faster at 4096x2048 and 4%
 // slower at 256x128x128; it keeps its run-time pitches.)
 template <int DIM>
@@ -72,7 +74,7 @@ struct FixedPitch<2> {
 };
 template <>
 struct FixedPitch<3> {
-  static constexpr int f[2] = {21, 192}, j[2] = {23, 256};
+  static constexpr int f[2] = {24, 216}, j[2] = {24, 264};
 };
 
 // Per-run constants, one entry per run in device memory.

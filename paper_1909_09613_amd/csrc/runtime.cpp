@@ -290,25 +290,39 @@ hipError_t host_copy(pic_ctx* c, void* dst, const void* src, size_t bytes, hipMe
   return e;
 }
 
-// Row and plane pitch of a staged window of w[0] x w[1] (x w[2]) nodes: in
-// mixed precision the fixed pitches of FixedPitch (fixed[2]: row, plane)
-// when the window fits them, so that the kernel's fixed-pitch variant runs;
-// else the window's own
-// row, and in 3D mixed precision a plane rounded up to a multiple of 8 (117
-// -> 120 nodes: 2% faster at 256x128x128 with 8x4x4 tiles, the LDS bank
-// conflicts of the wave's rows drop).  Measured on the benchmark workloads
-// (mixed precision): 2D field rows at 64 and current rows at 48 were 2%
-// faster at 4096x2048 than 48 for both, which was 1.8% faster than the bare
-// 41.
-void window_pitches(int ndim, bool f64, const int w[3], const int fixed[2], int p[2]) {
+// The smallest pitch >= w that is r modulo m.
+int pitch_from(int w, int r, int m) { return w + ((r - w) % m + m) % m; }
+
+// Row and plane pitch of a staged window of w[0] x w[1] (x w[2]) nodes.
+//
+// In mixed precision the fixed pitches of FixedPitch (fixed[2]: row, plane)
+// when the window fits them, so that the kernel's fixed-pitch variant runs
+// (2D: tiles of 16 cells along x1 and more).  Else, padded, the pitch that
+// puts the rows that the LDS serves together side by side on its banks: the
+// particles of a wave lie in the cells of the sort's order (x1 first; in 3D
+// mixed precision every second row before the others), and the LDS serves
+// 32 4-byte or 16 8-byte lanes at once, so a tile narrower than that has 2 or
+// 4 rows there, which start 16, 8 or 4 elements apart modulo 32 (16 in FP64).
+// Particle kernel, bare rows -> padded: 96x64x64 FP64 (4x4x4 tiles, rows 9 ->
+// 12) 616 -> 557 us, 256x128 cubic FP64 (8x8, 16 -> 24) 42.4 -> 35.4 us, 777x389
+// cubic FP64 (16x16, current rows 26 -> 40) 295 -> 289 us, 256x128 cubic mixed
+// (8x8, rows of the fixed pitches -> 24) 32.3 -> 29.5 us; 3D mixed precision as in
+// FixedPitch.
+void window_pitches(int ndim, bool f64, const int tile[3], const int w[3], const int fixed[2], bool pad, int p[2]) {
   p[0] = w[0];
-  p[1] = p[0] * w[1];
-  if (ndim == 3 && !f64) p[1] = (p[1] + 7) / 8 * 8;
-  const bool fits = !f64 && w[0] <= fixed[0] && (ndim == 2 || fixed[0] * w[1] <= fixed[1]);
-  if (fits) {
+  if (!f64 && w[0] <= fixed[0] && (ndim == 2 ? tile[0] >= 16 : fixed[0] * w[1] <= fixed[1])) {
     p[0] = fixed[0];
     p[1] = (ndim == 2) ? p[0] * w[1] : fixed[1];
+    return;
   }
+  if (pad) {
+    if (f64 || ndim == 2)
+      p[0] = tile[0] >= 8 ? pitch_from(w[0], 8, 16) : pitch_from(w[0], 4, 8);
+    else
+      p[0] = tile[0] >= 16 ? pitch_from(w[0], 8, 16) : pitch_from(w[0], 4, 8);
+  }
+  p[1] = p[0] * w[1];
+  if (ndim == 3 && !f64) p[1] = (pad && tile[0] < 16) ? pitch_from(p[1], 16, 32) : (p[1] + 7) / 8 * 8;
 }
 
 // Reach of a table's nodes relative to the particle's cell: base - cell is 0
@@ -460,15 +474,21 @@ pic_status apply_tiling(pic_ctx* c) {
   }
   const int* ffix = nd == 2 ? FixedPitch<2>::f : FixedPitch<3>::f;
   const int* jfix = nd == 2 ? FixedPitch<2>::j : FixedPitch<3>::j;
-  window_pitches(nd, c->f64(), c->fw, ffix, c->fp);
-  window_pitches(nd, c->f64(), c->jw, jfix, c->jp);
-  const size_t fcap = (size_t)(nd == 3 ? c->fp[1] * c->fw[2] : c->fp[0] * c->fw[1]);
-  const size_t jcap = (size_t)(nd == 3 ? c->jp[1] * c->jw[2] : c->jp[0] * c->jw[1]);
-  const size_t rs = sizeof(Real);
   // FP32: fine and coarse fixed-point current windows and a cell count in
   // 2D (7 ints per node), the fine windows in 3D (3 ints; its coarse ones
-  // are in global memory); FP64: FP64 current windows
-  c->lds = 6 * rs * fcap + (c->f64() ? 3 * sizeof(double) : (nd == 2 ? 7 : 3) * sizeof(int)) * jcap;
+  // are in global memory); FP64: FP64 current windows.  Padded rows where
+  // two groups still share a CU: both windows', the current's alone (its
+  // atomics lose more to conflicts than the reads), or none.
+  const size_t rs = sizeof(Real);
+  size_t jcap = 0;
+  for (int pad = 2; pad >= 0; --pad) {
+    window_pitches(nd, c->f64(), c->tile, c->fw, ffix, pad == 2, c->fp);
+    window_pitches(nd, c->f64(), c->tile, c->jw, jfix, pad >= 1, c->jp);
+    const size_t fcap = (size_t)(nd == 3 ? c->fp[1] * c->fw[2] : c->fp[0] * c->fw[1]);
+    jcap = (size_t)(nd == 3 ? c->jp[1] * c->jw[2] : c->jp[0] * c->jw[1]);
+    c->lds = 6 * rs * fcap + (c->f64() ? 3 * sizeof(double) : (nd == 2 ? 7 : 3) * sizeof(int)) * jcap;
+    if (c->lds <= std::min<size_t>(c->lds_budget, kDefaultLds)) break;
+  }
   if (nd == 3 && !c->f64() && 3 * jcap > (size_t)kCoarseCap)
     return c->fail(PIC_ERR_ARG, "tile too large for the coarse current windows");
   if (c->lds > (size_t)c->lds_budget) return c->fail(PIC_ERR_ARG, "tile and margin need more LDS than the workgroup budget");

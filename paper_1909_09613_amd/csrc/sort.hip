@@ -183,24 +183,25 @@ __global__ void sort_scatter(SortArgs<typename P::Real> A) {
   }
 }
 
-// Index of a particle's cell in the order the arrange pass lays cells out.
-// With an even tile width, in FP64 and for 2D tiles narrower than 32 cells:
-// first the cells of even x, then those of odd x (each in x-then-y-then-z
-// order), so that the lanes of a wave sit two cells apart along x and
-// particles that drift at slightly different times still fall in different
-// cells (same-address LDS atomics serialise).  Otherwise plain x-fastest
-// order.  Measured in 2D: FP64 16x16 5% faster with the split; mixed
-// precision 32x16 and 64x8 1-6% faster without it, 16x16 and 16x32 8-10%
-// faster with it; 3D mixed precision 3% faster without it.
+// Index of a particle's cell in the order the arrange pass lays cells out: x
+// first, then y, then z; in 3D mixed precision with an even number of rows
+// every second row of a plane before the others, so that the 32 lanes that
+// the LDS serves at once are two rows apart (their current atomics do not meet
+// where particles of one row start a row further than those of the other; with
+// the row pitches of FixedPitch they also lie on different banks).  With ranks
+// in the order of the offset, other orders are slower: cells of even x
+// before those of odd x (which kept neighbours' atomics apart when ranks were
+// in arrival order) 616 -> 631 us at 96x64x64 FP64 and 32.3 -> 37.5 us at 256x128
+// cubic mixed; 3D mixed at 128x128x64, with the pitches of that time: plain
+// order 740 us, every second row 719, every second plane 780, even x 733, even x
+// and rows 898 us.
 template <class P, int DIM>
 __device__ __forceinline__ int cell_index(const int c[3], const int org[3], const int tile[3]) {
   int m[3] = {0, 0, 0};
   for (int d = 0; d < DIM; ++d) m[d] = min(max(c[d] - org[d], 0), tile[d] - 1);
-  if ((P::kAbs || (DIM == 2 && tile[0] < 32)) && (tile[0] & 1) == 0) {
-    const int h = tile[0] >> 1;
-    const int rest = m[1] + tile[1] * m[2];
-    const int nrest = tile[1] * (DIM == 3 ? tile[2] : 1);
-    return (m[0] & 1) * h * nrest + rest * h + (m[0] >> 1);
+  if (!P::kAbs && DIM == 3 && (tile[1] & 1) == 0) {
+    const int h = tile[1] >> 1;
+    return m[0] + tile[0] * ((m[1] >> 1) + h * (m[2] + tile[2] * (m[1] & 1)));
   }
   int cl = 0, stride = 1;
   for (int d = 0; d < DIM; ++d) {
@@ -223,23 +224,24 @@ __device__ __forceinline__ int cell_in_tile(const PBuf<typename P::Real>& S, lon
 }
 
 // Order of a particle among those of its cell, as a 16-bit key: its offset
-// along x1, and in 3D first the half of the cell along x2 that it lies in.
-// The lanes of a wave hold one particle each of consecutive cells along x1,
-// all of the same rank, so with ranks in the order of the offset they lie at
-// about the same place in their cells.  Their stencils then mostly start at
-// the same node of their cell, and the lanes' LDS addresses stay distinct and
-// consecutive; where some lanes start one node further than others, the reads
-// conflict and the atomics of neighbouring cells meet at one address (LDS
-// cycles per 64-lane access at rows of 32 cells, with every lane's start
-// random: reads 3.4 against 2.7, 32-bit adds 6.5 against 4.5, FP64 adds 20.8
-// against 8.6).  A drift moves all particles of the wave alike and keeps the
-// order.  Particle kernel, against ranks in arrival order: 2D cubic 1024x512
-// mixed precision 347 -> 326 us, 777x389 FP64 334 -> 310 us; 3D quadratic
-// 128x128x64 mixed precision 779 -> 711 us (752 by the offset alone),
-// 96x64x64 FP64 716 -> 682 us.
-template <class Real, int DIM>
-__device__ __forceinline__ unsigned order_key(Real fx, Real fy) {
-  if (DIM == 2) return (unsigned)((float)fx * 65535.0f);
+// along x1, in 3D FP64 first the half of the cell along x2 that it lies in (a
+// group of 16 lanes then holds four rows).  The lanes of a wave hold one
+// particle each of consecutive cells along x1, all of the same rank, so with
+// ranks in the order of the offset they lie at about the same place in their
+// cells.  Their stencils then mostly start at the same node of their cell, and
+// the lanes' LDS addresses stay distinct and consecutive; where some lanes start
+// one node further than others, the reads conflict and the atomics of
+// neighbouring cells meet at one address (LDS cycles per 64-lane access at
+// rows of 32 cells, with every lane's start random: reads 3.4 against 2.7,
+// 32-bit adds 6.5 against 4.5, FP64 adds 20.8 against 8.6).  A drift moves all
+// particles of the wave alike and keeps the order.  Particle kernel, against
+// ranks in arrival order: 2D cubic 1024x512 mixed precision 347 -> 326 us, 777x389
+// FP64 334 -> 310 us.  3D, offset alone / half and offset: 128x128x64 mixed 670 /
+// 682 us, 96x64x64 FP64 576 / 557 us.
+template <class P, int DIM>
+__device__ __forceinline__ unsigned order_key(typename P::Real fx, typename P::Real fy) {
+  using Real = typename P::Real;
+  if (DIM == 2 || !P::kAbs) return (unsigned)((float)fx * 65535.0f);
   return (fy >= Real(0.5) ? 32768u : 0u) + (unsigned)((float)fx * 32767.0f);
 }
 
@@ -297,7 +299,7 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
           pc[v] = P::kAbs ? 0 : S.cell[q];
 #pragma unroll
           for (int d = 0; d < DIM; ++d)
-            if (P::kAbs || d < 2) x[v][d] = S.pos[d][q];
+            if (P::kAbs || d < 1) x[v][d] = S.pos[d][q];
         }
 #pragma unroll
         for (int v = 0; v < V; ++v) {
@@ -313,7 +315,7 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
             unpack_cell<DIM>(pc[v], c[0], c[1], c[2]);
           }
           const int cl = cell_index<P, DIM>(c, org, A.tile);
-          const unsigned k = order_key<Real, DIM>(x[v][0], x[v][1]);
+          const unsigned k = order_key<P, DIM>(x[v][0], x[v][1]);
           rank_of[u0 + v] = 0;
           if (tid + (u0 + v) * kArrangeBlock < n) rank_of[u0 + v] = atomicAdd(&cnt[cl], 1);
           cell_of[u0 + v] = cl | (int)(k << 16);

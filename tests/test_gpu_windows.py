@@ -73,3 +73,11 @@ def test_row_widths_3d(orc, tile, precision):
 def test_more_tiles_than_groups(orc, precision):
     # 64 x 48 tiles of 4 x 4 cells: more than the groups the chip holds at once
     _one_step(orc, RunSpec(2, (256, 192), 1, 0.45, 50.0, 0.01, 1, 822), precision, (4, 4, 1))
+
+
+@pytest.mark.parametrize("precision", PRECISIONS, ids=IDS)
+@pytest.mark.parametrize("order,tile", [(2, (4, 4, 4)), (3, (8, 4, 4)), (3, (4, 4, 4)), (2, (8, 8, 4)), (2, (8, 3, 4))])
+def test_padded_rows_3d(orc, order, tile, precision):
+    # rows padded in both windows, in the current's alone and in none (tiles
+    # that leave room for one group per CU), and an odd number of rows per plane
+    _one_step(orc, RunSpec(3, (18, 13, 11), order, 0.4, 50.0, 0.01, 1, 823), precision, tile)
