@@ -35,6 +35,12 @@ struct SortArgs {
   const int* tile_run;
 };
 
+// Block size, particles per thread and largest grid of the sort's count and
+// scatter passes.
+constexpr int kSortBlock = 512;
+constexpr int kSortItems = 4;
+constexpr int kSortGrid = 1024;
+
 // Block size and LDS bytes of the per-segment arrange pass of the sort.
 // Segments of up to kArrangeCap particles (kArrangeItems per thread) are
 // ordered by place within their cells (those of up to kArrangeOrderCount
