@@ -136,7 +136,7 @@ struct DevState {
   unsigned int arrange_done;   // sort arrange groups finished
   long long gpd_launches;      // particle-kernel launches completed
   unsigned int count_done;     // sort count groups finished
-  unsigned int pad1;
+  int io;                      // particle transfers: non-finite input, particles found (zero between calls)
 };
 
 // What a launch or a sort leaves for a tile's next step.

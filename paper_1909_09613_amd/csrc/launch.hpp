@@ -104,6 +104,25 @@ hipError_t launch_rho_tiles(const GpdArgs<typename P::Real>& a, int run, int nti
 template <class P>
 hipError_t launch_sort(const SortArgs<typename P::Real>& a, int ndim, hipStream_t s);
 
+// Particles of one species of one run between the caller's arrays (copied
+// to or from x and u, [n][3] doubles on the device) and the current store.
+template <class Real>
+struct IoArgs {
+  PBuf<Real> buf;     // the current store
+  double* x;
+  double* u;
+  long long n;        // particles of the species
+  long long base;     // load: the species' first place in the store; store: the run's
+  int species;
+  double cells[3];    // cells per axis
+};
+template <class P>
+hipError_t launch_io_check(const IoArgs<typename P::Real>& a, int ndim, int* flag, hipStream_t s);
+template <class P>
+hipError_t launch_io_load(const IoArgs<typename P::Real>& a, int ndim, hipStream_t s);
+template <class P>
+hipError_t launch_io_store(const IoArgs<typename P::Real>& a, int ndim, int* found, hipStream_t s);
+
 template <class Real>
 hipError_t launch_faraday_half(const FieldArgs<Real>& a, int ndim, bool m4, hipStream_t s);
 template <class Real>

@@ -733,60 +733,45 @@ void drop_graph(pic_ctx* c) {
 
 namespace {
 
-template <class Real>
-pic_status set_particles_t(pic_ctx* c, int run, int species, const double* x, const double* u,
-                                  int64_t n) {
+// The caller's arrays pass through the second particle store, which is free
+// between sorts: a species takes 48 bytes per particle there, the store has
+// at least 56 for each particle of one species (28 for each of both).
+template <class P>
+IoArgs<typename P::Real> io_args(pic_ctx* c, int run, int species) {
+  using Real = typename P::Real;
+  const RunHost& H = c->runs[run];
+  IoArgs<Real> a{};
+  a.buf = c->pbuf<Real>(0);
+  a.x = reinterpret_cast<double*>(c->P + c->lay.p_cell[1]);
+  a.u = a.x + 3 * H.nps;
+  a.n = H.nps;
+  a.base = H.p0;
+  a.species = species;
+  for (int k = 0; k < 3; ++k) a.cells[k] = H.n[k];
+  return a;
+}
+
+template <class P>
+pic_status set_particles_t(pic_ctx* c, int run, int species, const double* x, const double* u) {
   RunHost& H = c->runs[run];
   if (c->sorted_once) {
     // sorted stores interleave the species: the whole run must be re-set
     H.set[0] = H.set[1] = false;
   }
-  const long long base = H.p0 + species * H.nps;
-  std::vector<int> cell(c->f64() ? 0 : n), tag(n);
-  std::vector<Real> pos[3], uu[3];
-  for (int k = 0; k < 3; ++k) {
-    if (k < c->ndim) pos[k].resize(n);
-    uu[k].resize(n);
+  IoArgs<typename P::Real> a = io_args<P>(c, run, species);
+  a.base += species * H.nps;
+  const size_t bytes = sizeof(double) * 3 * H.nps;
+  hipError_t e = host_copy(c, a.x, x, bytes, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = host_copy(c, a.u, u, bytes, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = launch_io_check<P>(a, c->ndim, &c->state()->io, c->stream);
+  int bad = 0;
+  if (e == hipSuccess) e = host_copy(c, &bad, &c->state()->io, sizeof bad, hipMemcpyDeviceToHost);
+  if (e == hipSuccess && bad) {
+    const int zero = 0;
+    e = host_copy(c, &c->state()->io, &zero, sizeof zero, hipMemcpyHostToDevice);
+    if (e == hipSuccess) return c->fail(PIC_ERR_ARG, bad & 1 ? "non-finite position" : "non-finite momentum");
   }
-  for (int64_t i = 0; i < n; ++i) {
-    int cc[3] = {0, 0, 0};
-    for (int k = 0; k < c->ndim; ++k) {
-      double v = x[3 * i + k];
-      const double nd = H.n[k];
-      if (!std::isfinite(v)) return c->fail(PIC_ERR_ARG, "non-finite position");
-      v = std::fmod(v, nd);
-      while (v < 0.0) v += nd;
-      while (v >= nd) v -= nd;
-      if (c->f64()) {
-        pos[k][i] = Real(v);
-      } else {
-        double fl = std::floor(v);
-        float f = (float)(v - fl);
-        if (f >= 1.0f) {
-          f = 0.0f;
-          fl += 1.0;
-          if (fl >= nd) fl = 0.0;
-        }
-        cc[k] = (int)fl;
-        pos[k][i] = Real(f);
-      }
-    }
-    for (int k = 0; k < 3; ++k) {
-      if (!std::isfinite(u[3 * i + k])) return c->fail(PIC_ERR_ARG, "non-finite momentum");
-      uu[k][i] = Real(u[3 * i + k]);
-    }
-    if (!c->f64()) cell[i] = (c->ndim == 2) ? pack_cell<2>(cc[0], cc[1], 0) : pack_cell<3>(cc[0], cc[1], cc[2]);
-    tag[i] = (species << kSpeciesShift) | (int)i;
-  }
-  const size_t rs = sizeof(Real);
-  hipError_t e = hipSuccess;
-  if (!c->f64()) e = host_copy(c, c->P + c->lay.p_cell[0] + 4 * base, cell.data(), 4 * n, hipMemcpyHostToDevice);
-  for (int k = 0; k < c->ndim && e == hipSuccess; ++k)
-    e = host_copy(c, c->P + c->lay.p_pos[0][k] + rs * base, pos[k].data(), rs * n, hipMemcpyHostToDevice);
-  for (int k = 0; k < 3 && e == hipSuccess; ++k)
-    e = host_copy(c, c->P + c->lay.p_u[0][k] + rs * base, uu[k].data(), rs * n, hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = host_copy(c, c->P + c->lay.p_tag[0] + 4 * base, tag.data(), 4 * n, hipMemcpyHostToDevice);
+  if (e == hipSuccess) e = launch_io_load<P>(a, c->ndim, c->stream);
   const int one = 1;
   if (e == hipSuccess)
     e = host_copy(c, &c->state()->sort_request, &one, sizeof one, hipMemcpyHostToDevice);
@@ -798,51 +783,21 @@ pic_status set_particles_t(pic_ctx* c, int run, int species, const double* x, co
   return PIC_OK;
 }
 
-template <class Real>
-pic_status get_particles_t(pic_ctx* c, int run, int species, double* x, double* u, int64_t n) {
+template <class P>
+pic_status get_particles_t(pic_ctx* c, int run, int species, double* x, double* u) {
   const RunHost& H = c->runs[run];
-  const long long base = H.p0, cnt = 2 * H.nps;
-  const size_t rs = sizeof(Real);
-  std::vector<int> cell(c->f64() ? 0 : cnt), tag(cnt);
-  std::vector<Real> pos[3], uu[3];
-  hipError_t e = hipSuccess;
-  if (!c->f64()) e = host_copy(c, cell.data(), c->P + c->lay.p_cell[0] + 4 * base, 4 * cnt, hipMemcpyDeviceToHost);
-  for (int k = 0; k < 3; ++k) {
-    uu[k].resize(cnt);
-    if (e == hipSuccess)
-      e = host_copy(c, uu[k].data(), c->P + c->lay.p_u[0][k] + rs * base, rs * cnt, hipMemcpyDeviceToHost);
-    if (k < c->ndim) {
-      pos[k].resize(cnt);
-      if (e == hipSuccess)
-        e = host_copy(c, pos[k].data(), c->P + c->lay.p_pos[0][k] + rs * base, rs * cnt, hipMemcpyDeviceToHost);
-    }
-  }
-  if (e == hipSuccess) e = host_copy(c, tag.data(), c->P + c->lay.p_tag[0] + 4 * base, 4 * cnt, hipMemcpyDeviceToHost);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+  const IoArgs<typename P::Real> a = io_args<P>(c, run, species);
+  const size_t bytes = sizeof(double) * 3 * H.nps;
+  int found = 0;
+  const int zero = 0;
+  hipError_t e = launch_io_store<P>(a, c->ndim, &c->state()->io, c->stream);
+  if (e == hipSuccess) e = host_copy(c, &found, &c->state()->io, sizeof found, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = host_copy(c, &c->state()->io, &zero, sizeof zero, hipMemcpyHostToDevice);
   if (e != hipSuccess) return c->hip(e, "get_particles");
-  long long found = 0;
-  for (long long i = 0; i < cnt; ++i) {
-    const int sp = (tag[i] >> kSpeciesShift) & 1;
-    const long long id = tag[i] & ((1 << kSpeciesShift) - 1);
-    if (sp != species || id >= n) continue;
-    ++found;
-    int cc[3] = {0, 0, 0};
-    if (!c->f64()) {
-      if (c->ndim == 2)
-        unpack_cell<2>(cell[i], cc[0], cc[1], cc[2]);
-      else
-        unpack_cell<3>(cell[i], cc[0], cc[1], cc[2]);
-    }
-    for (int k = 0; k < 3; ++k) {
-      if (k < c->ndim)
-        x[3 * id + k] = c->f64() ? (double)pos[k][i] : (double)cc[k] + (double)pos[k][i];
-      else
-        x[3 * id + k] = 0.0;
-      u[3 * id + k] = (double)uu[k][i];
-    }
-  }
-  if (found != n) return c->fail(PIC_ERR_STATE, "particle identities are incomplete (were both species set?)");
-  return PIC_OK;
+  if (found != H.nps) return c->fail(PIC_ERR_STATE, "particle identities are incomplete (were both species set?)");
+  e = host_copy(c, x, a.x, bytes, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = host_copy(c, u, a.u, bytes, hipMemcpyDeviceToHost);
+  return c->hip(e, "get_particles");
 }
 
 template <class Real>
@@ -851,21 +806,24 @@ pic_status fields_io(pic_ctx* c, int run, const double* Ein, const double* Bin, 
   const RunHost& H = c->runs[run];
   const long long nc = H.ncell, NT = c->ncell_total;
   Real* F = static_cast<Real*>(c->F);
-  std::vector<Real> tmp(nc);
+  // FP64 input goes straight across; output passes through one buffer (copies
+  // into the caller's arrays, which may never have been touched, were slower)
+  constexpr bool same = std::is_same<Real, double>::value;
+  std::vector<Real> tmp(same && !Eout && !Bout ? 0 : nc);
   hipError_t e = hipSuccess;
   for (int comp = 0; comp < 6 && e == hipSuccess; ++comp) {
     const double* src = (comp < 3) ? Ein : Bin;
     double* dst = (comp < 3) ? Eout : Bout;
     const int k = comp % 3;
     Real* dev = F + comp * NT + H.cell0;
-    if (src) {
+    if (src && same) {
+      e = host_copy(c, dev, src + k * nc, sizeof(Real) * nc, hipMemcpyHostToDevice);
+    } else if (src) {
       for (long long i = 0; i < nc; ++i) tmp[i] = Real(src[k * nc + i]);
       e = host_copy(c, dev, tmp.data(), sizeof(Real) * nc, hipMemcpyHostToDevice);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     }
     if (dst && e == hipSuccess) {
       e = host_copy(c, tmp.data(), dev, sizeof(Real) * nc, hipMemcpyDeviceToHost);
-      if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
       for (long long i = 0; i < nc; ++i) dst[k * nc + i] = (double)tmp[i];
     }
   }
@@ -1140,7 +1098,7 @@ pic_status pic_set_particles(pic_ctx* c, int32_t run, int32_t species, const dou
   if (run < 0 || run >= c->nruns || species < 0 || species > 1) return c->fail(PIC_ERR_ARG, "bad run or species");
   if (!x || !u) return c->fail(PIC_ERR_ARG, "x and u must not be NULL");
   if (n != c->runs[run].nps) return c->fail(PIC_ERR_ARG, "n must equal ppc_per_species * ncell");
-  return c->f64() ? set_particles_t<double>(c, run, species, x, u, n) : set_particles_t<float>(c, run, species, x, u, n);
+  return c->f64() ? set_particles_t<F64>(c, run, species, x, u) : set_particles_t<F32>(c, run, species, x, u);
 }
 
 
@@ -1149,7 +1107,7 @@ pic_status pic_get_particles(pic_ctx* c, int32_t run, int32_t species, double* x
   if (run < 0 || run >= c->nruns || species < 0 || species > 1) return c->fail(PIC_ERR_ARG, "bad run or species");
   if (!x || !u) return c->fail(PIC_ERR_ARG, "x and u must not be NULL");
   if (n != c->runs[run].nps) return c->fail(PIC_ERR_ARG, "n must equal ppc_per_species * ncell");
-  return c->f64() ? get_particles_t<double>(c, run, species, x, u, n) : get_particles_t<float>(c, run, species, x, u, n);
+  return c->f64() ? get_particles_t<F64>(c, run, species, x, u) : get_particles_t<F32>(c, run, species, x, u);
 }
 
 
