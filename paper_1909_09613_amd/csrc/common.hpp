@@ -45,6 +45,13 @@ __host__ __device__ inline void unpack_cell(int c, int& x, int& y, int& z) {
     z = (c >> 22) & 0x3ff;
   }
 }
+// A packed cell moved by (dx, dy, dz) without leaving the grid.
+template <int DIM>
+__host__ __device__ inline int move_cell(int c, int dx, int dy, int dz) {
+  unsigned m = (unsigned)c + (unsigned)dx + ((unsigned)dy << (DIM == 2 ? 16 : 11));
+  if (DIM == 3) m += (unsigned)dz << 22;
+  return (int)m;
+}
 
 // Compile-time window pitches (elements; row, and plane in 3D) of the
 // mixed-precision particle kernel's fixed-pitch variant, per dimension.  A

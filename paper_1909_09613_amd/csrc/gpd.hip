@@ -23,7 +23,7 @@
 //   deposit  form-factor differences DS = S1 - S0 on the union of old and
 //            new nodes, evaluated as step * divided difference so that short
 //            transverse steps keep their precision in FP32; Esirkepov's
-//            decomposition W_x = DS_x (S0_y + DS_y/2) etc., prefix sums along
+//            decomposition W_x = DS_x Sh_y etc. with Sh = S0 + DS/2, prefix sums along
 //            each component's own axis.
 #include <climits>
 #include <type_traits>
@@ -52,13 +52,13 @@ struct Pair<double> {
 // below).  Just below the lower face that rounding can give t = 1: the
 // particle then stays on the face of its old cell (t = 0, dc = 0).
 template <class Real>
-__device__ __forceinline__ void cell_step(Real f, Real step, Real& t, int& dc) {
+__device__ __forceinline__ void cell_step(Real f, Real step, Real& t, Real& dc) {
   const Real x = f + step;
   const Real fl = floor(x);
   const Real r = x - fl;
   const bool up = r >= Real(1);
   t = up ? Real(0) : r;
-  dc = up ? 0 : (int)fl;
+  dc = up ? Real(0) : fl;
 }
 
 // The periodic image in [0, n) of a cell m = c + dc reached by a step dc in
@@ -177,6 +177,12 @@ __device__ __forceinline__ bool finite3(Real a, Real b, Real c) {
   return isfinite(a) && isfinite(b) && isfinite(c);
 }
 
+// m = max(m, |x|) of non-negative FP32 values held as their bit patterns, one
+// instruction (the compiler's maximum of an integer takes the absolute value
+// first, and that of a float quiets both operands first).
+__device__ __forceinline__ void max_abs(int& m, float x) { asm("v_max_f32 %0, %0, abs(%1)" : "+v"(m) : "v"(x)); }
+__device__ __forceinline__ void max_abs(int& m, double x) { m = max(m, __float_as_int((float)fabs(x))); }
+
 template <class Acc>
 __device__ __forceinline__ void lds_add(Acc* p, Acc v) {
   atomicAdd(p, v);
@@ -244,10 +250,10 @@ __device__ __forceinline__ unsigned fresh_off(unsigned o) {
   return o;
 }
 
-// m mod n for -n <= m < n, without an integer division or a compare: the
-// sign bit selects n.  A cell index and the box's periodic low end, both
-// reduced to [0, n), differ by less than n.
-__device__ __forceinline__ int wrap_once(int m, int n) { return m + (n & (m >> 31)); }
+// m mod n for -n <= m < n, two instructions: of m and m + n the one in [0, n)
+// is the smaller as an unsigned number.  A cell index and the box's periodic
+// low end, both reduced to [0, n), differ by less than n.
+__device__ __forceinline__ int wrap_once(int m, int n) { return (int)min((unsigned)m, (unsigned)(m + n)); }
 
 // m mod n for any m, by subtraction: a tile's windows start within a few
 // periods of [0, n), nearly always in it (an integer division takes some
@@ -658,31 +664,79 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
   }
   int bmin[3] = {INT_MAX, INT_MAX, INT_MAX}, bmax[3] = {INT_MIN, INT_MIN, INT_MIN};
   int nbad = 0, noor = 0;
-  const Real third = Real(1) / Real(3);
+  const Real twelfth = Real(1) / Real(12);
   const Real half = Real(0.5);
-  // per-axis constants of the loop: the periodic image of a particle's cell
-  // is rel = wrap(c - co, n) + lo, and it must lie in [rlo, rhi] for the
-  // staged windows; window offsets of the half-lattice, T and union stencils
+  // per-axis constants of the loop.  A particle's place along an axis is
+  // q = wrap(c - co, n), counted from lo (tile-relative), the lowest place
+  // whose stencils the staged windows hold; they hold those up to qmax.
+  // Counted from there the test is one compare, and the windows' offsets
+  // (half-lattice, T and union stencils, cell counts) take lo in.  Where the
+  // windows are wider than the axis, every cell has a place in them, and the
+  // box is centred in the axis's n places as far as the windows reach.
+  // In an inner tile, whose places all lie inside the grid with a cell to
+  // spare below and two above (a position can round up onto a cell face),
+  // c - co needs no wrap and a moved particle's cell no periodic image, some
+  // twenty vector instructions of 600 per particle.  With the waves' stencil
+  // changes as masks, the box's low end in the windows' offsets and the deposit
+  // from S0 + DS/2, particle kernel at 2048 x 1024 cubic mixed 607 -> 595 us,
+  // 1024 x 512 304 -> 299 us.
   // (kept in vector registers on the FP32 path, where scalar registers run
   // out; the FP64 path and the 512-thread 3D kernel need their vector
   // registers for their own state, within 128 for four waves per SIMD)
   auto pin = [](int x) { return (P::kAbs || (DIM == 3 && GpdShape<L, DIM, SKIP>::kWide)) ? x : in_vgpr(x); };
-  int co[3], lo_[3], nn[3], rlo[3], rhi[3], hoff[3], toff[3], uoff[3], jo_[3];
+  int co[3], lo_[3], nn[3], qmax[3], hoff[3], toff[3], uoff[3], joff[3];
+  bool inside = true;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
     const int n = R.n[d];
     const int slack = max(0, n - 1 - (bb[2 * d + 1] - bb[2 * d]));
-    const int lo = bb[2 * d] - (slack >> 1);
-    co[d] = pin(wrap_sub(org[d] + lo, n));
-    lo_[d] = pin(lo);
+    const int rlo = max(fo[d] - R.glo[d], jo[d] - R.dlo[d]);
+    const int rhi = min(fo[d] + fs[d] - 1 - R.ghi[d], jo[d] + jsz[d] - 1 - R.dhi[d]);
+    const int lo = (rhi - rlo < n) ? rlo : min(max(bb[2 * d] - (slack >> 1), rlo), rhi - n + 1);
+    const int c0 = wrap_sub(org[d] + lo, n);
+    lo_[d] = lo;
+    if (d < DIM) inside = inside && c0 >= 1 && c0 + (rhi - lo) <= n - 3;
+    co[d] = pin(c0);
     nn[d] = pin(n);
-    rlo[d] = pin(max(fo[d] - R.glo[d], jo[d] - R.dlo[d]));
-    rhi[d] = pin(min(fo[d] + fs[d] - 1 - R.ghi[d], jo[d] + jsz[d] - 1 - R.dhi[d]));
-    hoff[d] = pin(kWh.first - fo[d]);
-    toff[d] = pin(R.tf[d].first - fo[d]);
-    uoff[d] = pin(kWi.first - jo[d]);
-    jo_[d] = pin(jo[d]);
+    qmax[d] = pin(min(rhi - lo, n - 1));
+    hoff[d] = pin(kWh.first - fo[d] + lo);
+    toff[d] = pin(R.tf[d].first - fo[d] + lo);
+    uoff[d] = pin(kWi.first - jo[d] + lo);
+    joff[d] = pin(lo - jo[d]);
   }
+  // (one scalar, so that the loop branches on it with a scalar compare)
+  int inner = __builtin_amdgcn_readfirstlane(inside ? 1 : 0);
+  asm volatile("" : "+s"(inner));
+  auto place = [&](const int* c, int* q) {
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) q[d] = c[d] - co[d];
+    if (!inner) {
+      asm volatile("");  // (a branch of the wave, no selects)
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) q[d] = wrap_once(q[d], nn[d]);
+    }
+    bool in = true;
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) in = in && (unsigned)q[d] <= (unsigned)qmax[d];
+    return in;
+  };
+  // the packed cell of a particle that moved by dc cells from cell c (packed: cw)
+  auto moved_cell = [&](int cw, const int* c, const int* dc) {
+    if (inner) return move_cell<DIM>(cw, dc[0], dc[1], dc[2]);
+    int m[3] = {0, 0, 0};
+#pragma unroll
+    for (int d = 0; d < DIM; ++d) m[d] = wrap_step(c[d] + dc[d], nn[d]);
+    return pack_cell<DIM>(m[0], m[1], m[2]);
+  };
+  // a position in [0, n) (FP64: cell and offset in one)
+  auto wrap_pos = [&](Real x, int d) {
+    if (!inner) {
+      const Real nd = Real(R.n[d]);
+      while (x < Real(0)) x += nd;
+      while (x >= nd) x -= nd;
+    }
+    return x;
+  };
   // offset along axis d in the current and count windows (their row and
   // plane pitch; compile-time constants in the 2D variant with fixed pitches)
   auto cwin = [&](int d, int r) { return d == 0 ? r : imul24(r, d == 1 ? jpx : jpz); };
@@ -692,63 +746,58 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
   // velocity (the arithmetic of the move in the loop below) and deposits no
   // current; it still counts for the box, the cell counts and the next
   // step's fixed-point bounds
-  auto drift = [&](unsigned o_in, const int* c, const Real* f, const Real* xo, Real u0, Real u1, Real u2, const int* rel) {
+  auto drift = [&](unsigned o_in, int cell, const int* c, const Real* f, const Real* xo, Real u0, Real u1, Real u2,
+                   const int* q) {
     const unsigned o = fresh_off(o_in);
     const Real ig = fast_rsqrt(Real(1) + u0 * u0 + u1 * u1 + u2 * u2);
     const Real vd[3] = {u0 * ig, u1 * ig, u2 * ig};
-    int cwi = 0, cw[3] = {0, 0, 0};
+    int cwi = 0, dci[3] = {0, 0, 0};
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
       const Real step = R.a[d] * vd[d];
-      int cnd;
       Real ddd;
       if (P::kAbs) {
         const Real xn = xo[d] + step;
-        cnd = (int)floor(xn);
+        dci[d] = (int)floor(xn) - c[d];
         ddd = xn - xo[d];
-        Real w = xn;
-        const Real nd = Real(R.n[d]);
-        while (w < Real(0)) w += nd;
-        while (w >= nd) w -= nd;
-        at(B.pos[d], o) = w;
+        at(B.pos[d], o) = wrap_pos(xn, d);
       } else {
-        Real t;
-        int dc;
+        Real t, dc;
         cell_step(f[d], step, t, dc);
-        cnd = c[d] + dc;
-        ddd = (t - f[d]) + Real(dc);
+        dci[d] = (int)dc;
+        ddd = (t - f[d]) + dc;
         at(B.pos[d], o) = t;
-        cw[d] = wrap_step(cnd, R.n[d]);
       }
       // a drifting particle still bounds the next step's fixed-point scale
-      if (kFix) mnew[d] = max(mnew[d], __float_as_int((float)fabs(ddd)));
-      const int rn = rel[d] + (cnd - c[d]);
-      bmin[d] = min(bmin[d], rn);
-      bmax[d] = max(bmax[d], rn);
-      cwi += cwin(d, rn - jo_[d]);
+      if (kFix) max_abs(mnew[d], ddd);
+      const int qn = q[d] + dci[d];
+      bmin[d] = min(bmin[d], qn);
+      bmax[d] = max(bmax[d], qn);
+      cwi += cwin(d, qn + joff[d]);
     }
-    if (kFix && DIM == 2) mnew[2] = max(mnew[2], __float_as_int((float)fabs(vd[2])));
+    if (kFix && DIM == 2) max_abs(mnew[2], vd[2]);
     if (kCnt) atomicAdd(Cw + cwi, 1);
-    if (!P::kAbs) at(B.cell, o) = pack_cell<DIM>(cw[0], cw[1], cw[2]);
+    if (!P::kAbs) at(B.cell, o) = moved_cell(cell, c, dci);
   };
   if (SKIP && smode == 1) {
     // every particle of the tile drifts: several particles per thread with
     // their loads issued together (this loop is bound by memory latency)
     constexpr int U = 4;
     for (int p0 = sA + tid; p0 < sC; p0 += U * nth) {
-      int cc[U][3];
+      int cc[U][3], cw[U];
       Real ff[U][3], xx[U][3], uu[U][3];
 #pragma unroll
       for (int k = 0; k < U; ++k) {
         const unsigned o = part_off<Real>(min(p0 + k * nth, sC - 1) - sA);
-        cc[k][0] = cc[k][1] = cc[k][2] = 0;
+        cc[k][0] = cc[k][1] = cc[k][2] = cw[k] = 0;
 #pragma unroll
         for (int d = 0; d < 3; ++d) ff[k][d] = xx[k][d] = Real(0);
         if (P::kAbs) {
 #pragma unroll
           for (int d = 0; d < DIM; ++d) xx[k][d] = at(B.pos[d], o);
         } else {
-          unpack_cell<DIM>(at(B.cell, o), cc[k][0], cc[k][1], cc[k][2]);
+          cw[k] = at(B.cell, o);
+          unpack_cell<DIM>(cw[k], cc[k][0], cc[k][1], cc[k][2]);
 #pragma unroll
           for (int d = 0; d < DIM; ++d) ff[k][d] = at(B.pos[d], o);
         }
@@ -768,19 +817,12 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
             ff[k][d] = xx[k][d] - fl;
           }
         }
-        int rel[3] = {0, 0, 0};
-        bool inwin = true;
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) {
-          const int rr = wrap_once(cc[k][d] - co[d], nn[d]) + lo_[d];
-          rel[d] = rr;
-          inwin = inwin && rr >= rlo[d] && rr <= rhi[d];
-        }
-        if (!inwin) {
+        int q[3] = {0, 0, 0};
+        if (!place(cc[k], q)) {
           ++noor;
           continue;
         }
-        drift(part_off<Real>(p - sA), cc[k], ff[k], xx[k], uu[k][0], uu[k][1], uu[k][2], rel);
+        drift(part_off<Real>(p - sA), cw[k], cc[k], ff[k], xx[k], uu[k][0], uu[k][1], uu[k][2], q);
       }
     }
   }
@@ -789,7 +831,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     const int sp = (p >= sB) ? 1 : 0;
     const unsigned o = part_off<Real>(p - sA);
     // ---- load ---------------------------------------------------------
-    int c[3] = {0, 0, 0};
+    int c[3] = {0, 0, 0}, cell = 0;
     Real f[3] = {Real(0), Real(0), Real(0)};
     Real xo[3] = {Real(0), Real(0), Real(0)};
     if (P::kAbs) {
@@ -801,7 +843,8 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
         f[d] = xo[d] - fl;
       }
     } else {
-      unpack_cell<DIM>(at(B.cell, o), c[0], c[1], c[2]);
+      cell = at(B.cell, o);
+      unpack_cell<DIM>(cell, c[0], c[1], c[2]);
 #pragma unroll
       for (int d = 0; d < DIM; ++d) f[d] = at(B.pos[d], o);
     }
@@ -811,17 +854,8 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     // window test, a second memory round trip per particle)
     asm volatile("" ::"v"(u0), "v"(u1), "v"(u2), "v"(f[0]), "v"(f[1]), "v"(f[DIM - 1]), "v"(xo[0]));
 
-    int rel[3] = {0, 0, 0};
-    bool inwin = true;
-#pragma unroll
-    for (int d = 0; d < DIM; ++d) {
-      // periodic image nearest the box: rel in [lo, lo + n), the box centred
-      // in that range (a box as wide as the axis starts it)
-      const int rr = wrap_once(c[d] - co[d], nn[d]) + lo_[d];
-      rel[d] = rr;
-      inwin = inwin && rr >= rlo[d] && rr <= rhi[d];
-    }
-    if (!inwin) {
+    int q[3] = {0, 0, 0};
+    if (!place(c, q)) {
       ++noor;
       continue;
     }
@@ -834,7 +868,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
         drifting = !skip_perturbed<DIM>(R, xa, ct);
       }
       if (drifting) {
-        drift(o, c, f, xo, u0, u1, u2, rel);
+        drift(o, cell, c, f, xo, u0, u1, u2, q);
         continue;
       }
     }
@@ -847,9 +881,9 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     auto weights_h = [&](int d, const Tab<Real>& Th) {
       int b;
       Real gg;
-      tab_split(Th, c[d], f[d], b, gg);
+      tab_split(Th, 0, f[d], b, gg);
       wtab_eval<L, NW>(Th, gg, wh[d]);
-      ih[d] = rel[d] + (b - c[d]) + hoff[d];
+      ih[d] = q[d] + b + hoff[d];
     };
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
@@ -857,10 +891,10 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
       else weights_h(d, R.Wh[d]);
       int b;
       Real gg;
-      split_rt(R.tf[d].sigma, c[d], f[d], b, gg);
+      split_rt(R.tf[d].sigma, 0, f[d], b, gg);
       if constexpr (kMoments) tfac_eval<L>(R.tf[d], gg, wt[d]);
       else tab_eval<L, KT, true>(R.T[d], gg, wt[d], kTop ? ttop[d] : nullptr);
-      it[d] = rel[d] + (b - c[d]) + toff[d];
+      it[d] = q[d] + b + toff[d];
     }
 
     // ---- gather ------------------------------------------------------------
@@ -913,7 +947,8 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     const Real eps = spc[4 * sp];
     const Real umx = u0 + eps * E0, umy = u1 + eps * E1, umz = u2 + eps * E2;
     const Real igm = fast_rsqrt(Real(1) + umx * umx + umy * umy + umz * umz);
-    const Real tx = eps * B0 * igm, ty = eps * B1 * igm, tz = eps * B2 * igm;
+    const Real egm = eps * igm;
+    const Real tx = B0 * egm, ty = B1 * egm, tz = B2 * egm;
     const Real s2 = Real(2) * fast_rcp(Real(1) + tx * tx + ty * ty + tz * tz);
     const Real sx = s2 * tx, sy = s2 * ty, sz = s2 * tz;
     const Real upx = umx + (umy * tz - umz * ty);
@@ -928,9 +963,9 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
       int cwi = 0;
 #pragma unroll
       for (int d = 0; d < DIM; ++d) {
-        bmin[d] = min(bmin[d], rel[d]);
-        bmax[d] = max(bmax[d], rel[d]);
-        cwi += cwin(d, rel[d] - jo_[d]);
+        bmin[d] = min(bmin[d], q[d]);
+        bmax[d] = max(bmax[d], q[d]);
+        cwi += cwin(d, q[d] + joff[d]);
       }
       if (kCnt) atomicAdd(Cw + cwi, 1);
       continue;
@@ -942,7 +977,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     // ---- move ------------------------------------------------------------
     const Real igam = fast_rsqrt(Real(1) + u0 * u0 + u1 * u1 + u2 * u2);
     const Real vv[3] = {u0 * igam, u1 * igam, u2 * igam};
-    int cn[3] = {0, 0, 0};
+    int dci[3] = {0, 0, 0};
     Real fn[3] = {Real(0), Real(0), Real(0)}, dd[3] = {Real(0), Real(0), Real(0)};
     Real xw[3] = {Real(0), Real(0), Real(0)};
 #pragma unroll
@@ -951,69 +986,72 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
       if (P::kAbs) {
         const Real xn = xo[d] + step;
         const Real fl = floor(xn);
-        cn[d] = (int)fl;
+        dci[d] = (int)fl - c[d];
         fn[d] = xn - fl;
         dd[d] = xn - xo[d];
-        Real w = xn;
-        const Real nd = Real(R.n[d]);
-        while (w < Real(0)) w += nd;
-        while (w >= nd) w -= nd;
-        xw[d] = w;
+        xw[d] = wrap_pos(xn, d);
       } else {
-        Real t;
-        int dc;
+        Real t, dc;
         cell_step(f[d], step, t, dc);
         fn[d] = t;
-        cn[d] = c[d] + dc;
-        dd[d] = (t - f[d]) + Real(dc);
+        dci[d] = (int)dc;
+        dd[d] = (t - f[d]) + dc;
       }
     }
 
     // ---- form factors and their differences on the union stencil -----------
-    Real S0u[3][NU], DSu[3][NU];
+    // (the deposit takes the shape at half the step, Sh = S0 + DS/2, and DS)
+    Real Sh[3][NU], DSu[3][NU];
     int iu[3] = {0, 0, 0};
     bool cross[3] = {false, false, false};  // union stencil one node wider than S0
     auto form_factors = [&](int d, const Tab<Real>& Tw) {
       int b0, b1;
       Real g0, g1;
-      tab_split(Tw, c[d], f[d], b0, g0);
-      tab_split(Tw, cn[d], fn[d], b1, g1);
+      tab_split(Tw, 0, f[d], b0, g0);
+      tab_split(Tw, dci[d], fn[d], b1, g1);
       Real s0[NW], s1[NW], dA[NW], dB[NW], a0[NU], ds[NU];
       wtab_eval<L, NW>(Tw, g0, s0);
       const int db = b1 - b0;
-      cross[d] = db != 0;
-      const bool shA = db < 0, shB = db > 0;
-      iu[d] = rel[d] + (min(b0, b1) - c[d]) + uoff[d];
+      // lanes whose new stencil starts one node lower, one higher: the
+      // tests below and the deposit's take them from these two compares
+      const unsigned long long lower = __builtin_amdgcn_ballot_w64(db < 0);
+      const unsigned long long upper = __builtin_amdgcn_ballot_w64(db > 0);
+      const bool shA = __builtin_amdgcn_inverse_ballot_w64(lower);
+      const bool shB = __builtin_amdgcn_inverse_ballot_w64(upper);
+      cross[d] = __builtin_amdgcn_inverse_ballot_w64(lower | upper);
+      iu[d] = q[d] + min(b0, b1) + uoff[d];
       // Node k of the union is node k of S0 unless the new stencil starts one
-      // node lower (shA), then node k - 1.  A wave whose steps are all short
-      // and none of which changed its stencil takes the cheapest form.
-      if (__all(fabs(dd[d]) >= Real(0.0625))) {
+      // node lower (shA), then node k - 1.
+#pragma unroll
+      for (int k = 0; k < NU; ++k) a0[k] = k < NW ? s0[k] : Real(0);
+      if (lower != 0) {
+        asm volatile("");  // (a branch of the wave, not ten selects)
+#pragma unroll
+        for (int k = NU - 1; k >= 0; --k) a0[k] = shA ? (k >= 1 ? a0[k - 1] : Real(0)) : a0[k];
+      }
+      // A wave whose steps are all short and none of which changed its
+      // stencil takes the cheapest form.
+      if (__builtin_amdgcn_ballot_w64(fabs(dd[d]) < Real(0.0625)) == 0) {
         // every step of the wave is long: S1 - S0 directly keeps its
         // precision (rounding of order one against |step| >= 1/16)
         wtab_eval<L, NW>(Tw, g1, s1);
 #pragma unroll
-        for (int k = 0; k < NU; ++k) {
-          a0[k] = shA ? (k >= 1 ? s0[k - 1] : Real(0)) : (k < NW ? s0[k] : Real(0));
-          const Real a1 = shB ? (k >= 1 ? s1[k - 1] : Real(0)) : (k < NW ? s1[k] : Real(0));
-          ds[k] = a1 - a0[k];
-        }
-      } else if (!__any(db != 0)) {
+        for (int k = 0; k < NU; ++k)
+          ds[k] = (shB ? (k >= 1 ? s1[k - 1] : Real(0)) : (k < NW ? s1[k] : Real(0))) - a0[k];
+      } else if ((lower | upper) == 0) {
         // no lane of the wave changed its stencil: one divided difference
         wtab_diff<L, kConst>(Tw, g0, g1, dd[d], dA);
 #pragma unroll
-        for (int k = 0; k < NU; ++k) {
-          a0[k] = k < NW ? s0[k] : Real(0);
-          ds[k] = k < NW ? dA[k] : Real(0);
-        }
+        for (int k = 0; k < NU; ++k) ds[k] = k < NW ? dA[k] : Real(0);
       } else {
         // a stencil that moved splits its difference at the lattice point
         // it crossed (an end of g's range)
-        const Real eA = (db == 0) ? g1 : (db > 0 ? Real(1) : Real(0));
-        const Real lA = (db == 0) ? dd[d] : (db > 0 ? Real(1) - g0 : -g0);
+        const Real eA = cross[d] ? (shB ? Real(1) : Real(0)) : g1;
+        const Real lA = cross[d] ? (shB ? Real(1) - g0 : -g0) : dd[d];
         wtab_diff<L, kConst>(Tw, g0, eA, lA, dA);
-        if (db != 0) {
-          const Real sBv = (db > 0) ? Real(0) : Real(1);
-          const Real lB = (db > 0) ? g1 : g1 - Real(1);
+        if (cross[d]) {
+          const Real sBv = shB ? Real(0) : Real(1);
+          const Real lB = shB ? g1 : g1 - Real(1);
           wtab_diff<L, kConst>(Tw, sBv, g1, lB, dB);
         } else {
 #pragma unroll
@@ -1021,7 +1059,6 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
         }
 #pragma unroll
         for (int k = 0; k < NU; ++k) {
-          a0[k] = shA ? (k >= 1 ? s0[k - 1] : Real(0)) : (k < NW ? s0[k] : Real(0));
           const Real da = shA ? (k >= 1 ? dA[k - 1] : Real(0)) : (k < NW ? dA[k] : Real(0));
           const Real dbv = shB ? (k >= 1 ? dB[k - 1] : Real(0)) : (k < NW ? dB[k] : Real(0));
           ds[k] = da + dbv;
@@ -1029,7 +1066,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
       }
 #pragma unroll
       for (int k = 0; k < NU; ++k) {
-        S0u[d][k] = a0[k];
+        Sh[d][k] = fma(half, ds[k], a0[k]);
         DSu[d][k] = ds[k];
       }
     };
@@ -1057,7 +1094,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
 #pragma unroll
         for (int v = 0; v < NU; ++v) {
           if (v == L + 1 && !cross[1]) continue;
-          const Real fy = kx * (S0u[1][v] + half * DSu[1][v]);
+          const Real fy = kx * Sh[1][v];
           const int ro = jpx * v;
           Real acc = ox;
 #pragma unroll
@@ -1070,7 +1107,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
           if (u == L + 1 && !cross[0]) continue;
-          const Real fx = ky * (S0u[0][u] + half * DSu[0][u]);
+          const Real fx = ky * Sh[0][u];
           Real acc = oy;
 #pragma unroll
           for (int v = 0; v < L; ++v) {
@@ -1079,34 +1116,34 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
           }
           if (cross[1]) sink(1, jb + (u + jpx * L), acc + DSu[1][L] * fx);
         }
-        const Real vz = kz * vv[2];
+        // the path average of S_x S_y is Sh_x Sh_y + DS_x DS_y / 12
+        const Real vz = kz * vv[2], vz12 = vz * twelfth;
 #pragma unroll
         for (int v = 0; v < NU; ++v) {
           if (v == L + 1 && !cross[1]) continue;
-          const Real Av = vz * (S0u[1][v] + half * DSu[1][v]);
-          const Real Bv = vz * (half * S0u[1][v] + third * DSu[1][v]);
+          const Real Av = vz * Sh[1][v];
+          const Real Bv = vz12 * DSu[1][v];
           const int ro = jpx * v;
 #pragma unroll
           for (int u = 0; u <= L; ++u)
             sink(2, jb + (ro + u),
-                 kFix ? fma(S0u[0][u], Av, fma(DSu[0][u], Bv, oz)) : S0u[0][u] * Av + DSu[0][u] * Bv);
+                 kFix ? fma(Sh[0][u], Av, fma(DSu[0][u], Bv, oz)) : Sh[0][u] * Av + DSu[0][u] * Bv);
           if (cross[0])
-            sink(2, jb + (ro + L + 1), kFix ? fma(S0u[0][L + 1], Av, fma(DSu[0][L + 1], Bv, oz))
-                                            : S0u[0][L + 1] * Av + DSu[0][L + 1] * Bv);
+            sink(2, jb + (ro + L + 1), kFix ? fma(Sh[0][L + 1], Av, fma(DSu[0][L + 1], Bv, oz))
+                                            : Sh[0][L + 1] * Av + DSu[0][L + 1] * Bv);
         }
       } else {
-        // path averages of the transverse shapes: (S0 + DS/2) and (S0/2 + DS/3)
-        // enter as S0_b (S0_c + DS_c/2) + DS_b (S0_c/2 + DS_c/3); the prefix
-        // sums run over DS scaled by the component's current scale, from the
-        // component's offset, so that a node's value is the running sum itself
+        // path averages of the transverse shapes: Sh_b Sh_c + DS_b DS_c / 12;
+        // the prefix sums run over DS scaled by the component's current scale,
+        // from the component's offset, so that a node's value is the running
+        // sum itself
         const Real ks[3] = {kx, ky, kz};
-        Real pa[3][NU], pb[3][NU], dk[3][NU];
+        Real pb[3][NU], dk[3][NU];
 #pragma unroll
         for (int d = 0; d < 3; ++d)
 #pragma unroll
           for (int k = 0; k < NU; ++k) {
-            pa[d][k] = S0u[d][k] + half * DSu[d][k];
-            pb[d][k] = half * S0u[d][k] + third * DSu[d][k];
+            pb[d][k] = twelfth * DSu[d][k];
             dk[d][k] = ks[d] * DSu[d][k];
           }
         // J1: prefix along x of DS_x * T_yz
@@ -1115,7 +1152,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
 #pragma unroll
           for (int v = 0; v < NU; ++v) {
             if ((v == L + 1 && !cross[1]) || (w == L + 1 && !cross[2])) continue;
-            const Real tr = S0u[1][v] * pa[2][w] + DSu[1][v] * pb[2][w];
+            const Real tr = Sh[1][v] * Sh[2][w] + DSu[1][v] * pb[2][w];
             const int ro = jpx * v + jpz * w;
             Real acc = ox;
 #pragma unroll
@@ -1131,7 +1168,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
             if ((u == L + 1 && !cross[0]) || (w == L + 1 && !cross[2])) continue;
-            const Real tr = S0u[0][u] * pa[2][w] + DSu[0][u] * pb[2][w];
+            const Real tr = Sh[0][u] * Sh[2][w] + DSu[0][u] * pb[2][w];
             const int co = u + jpz * w;
             Real acc = oy;
 #pragma unroll
@@ -1147,7 +1184,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
 #pragma unroll
           for (int u = 0; u < NU; ++u) {
             if ((u == L + 1 && !cross[0]) || (v == L + 1 && !cross[1])) continue;
-            const Real tr = S0u[0][u] * pa[1][v] + DSu[0][u] * pb[1][v];
+            const Real tr = Sh[0][u] * Sh[1][v] + DSu[0][u] * pb[1][v];
             const int co = u + jpx * v;
             Real acc = oz;
 #pragma unroll
@@ -1169,9 +1206,9 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
       // particle's other components stay in the fine windows (a kick along
       // one axis leaves the others' precision alone)
       const Real m0 = fabs(dd[0]), m1 = fabs(dd[1]), m2 = (DIM == 2) ? fabs(vv[2]) : fabs(dd[2]);
-      mnew[0] = max(mnew[0], __float_as_int((float)m0));
-      mnew[1] = max(mnew[1], __float_as_int((float)m1));
-      mnew[2] = max(mnew[2], __float_as_int((float)m2));
+      max_abs(mnew[0], m0);
+      max_abs(mnew[1], m1);
+      max_abs(mnew[2], m2);
       if (m0 <= thr[0] && m1 <= thr[1] && m2 <= thr[2]) {
         deposit([&](int c, int i, Real v) { lds_addq(Qf + c * jcap + i, v); }, ksp[0], ksp[1], ksp[2], half, half,
                 half);
@@ -1195,10 +1232,10 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     int cwi = 0;
 #pragma unroll
     for (int d = 0; d < DIM; ++d) {
-      const int rn = rel[d] + (cn[d] - c[d]);
-      bmin[d] = min(bmin[d], rn);
-      bmax[d] = max(bmax[d], rn);
-      cwi += cwin(d, rn - jo_[d]);
+      const int qn = q[d] + dci[d];
+      bmin[d] = min(bmin[d], qn);
+      bmax[d] = max(bmax[d], qn);
+      cwi += cwin(d, qn + joff[d]);
     }
     if (kCnt) atomicAdd(Cw + cwi, 1);
     const unsigned os = fresh_off(o);
@@ -1206,13 +1243,9 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
 #pragma unroll
       for (int d = 0; d < DIM; ++d) at(B.pos[d], os) = xw[d];
     } else {
-      int cw[3] = {0, 0, 0};
 #pragma unroll
-      for (int d = 0; d < DIM; ++d) {
-        cw[d] = wrap_step(cn[d], R.n[d]);
-        at(B.pos[d], os) = fn[d];
-      }
-      at(B.cell, os) = pack_cell<DIM>(cw[0], cw[1], cw[2]);
+      for (int d = 0; d < DIM; ++d) at(B.pos[d], os) = fn[d];
+      at(B.cell, os) = moved_cell(cell, c, dci);
     }
     at(B.u[0], os) = u0;
     at(B.u[1], os) = u1;
@@ -1301,6 +1334,9 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
         if (lo > hi) {  // no particles: keep the tile rectangle
           lo = 0;
           hi = min(A.tile[d], R.n[d] - org[d]) - 1;
+        } else {
+          lo += lo_[d];
+          hi += lo_[d];
         }
         need = need || (hi - lo > A.guard[d]);
         // a box that drifted a whole period keeps canonical coordinates
