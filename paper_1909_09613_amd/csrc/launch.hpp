@@ -46,8 +46,8 @@ constexpr int kSortGrid = 1024;
 // ordered by place within their cells (those of up to kArrangeOrderCount
 // particles), in tiles of up to kArrangeOrderCells cells (the tables of larger
 // ones leave no room for the keys in 64 KB).
-constexpr int kArrangeBlock = 512;
-constexpr int kArrangeItems = 16;
+constexpr int kArrangeBlock = 1024;
+constexpr int kArrangeItems = 8;
 constexpr int kArrangeCap = kArrangeItems * kArrangeBlock;
 constexpr int kArrangeOrderCells = 2048, kArrangeOrderCount = 64;
 inline size_t arrange_lds(int tc, int kcap) {

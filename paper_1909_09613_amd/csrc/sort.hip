@@ -297,8 +297,18 @@ __device__ __forceinline__ unsigned order_key(typename P::Real fx, typename P::R
   return (fy >= Real(0.5) ? 32768u : 0u) + (unsigned)((float)fx * 32767.0f);
 }
 
+// Each particle's slot is found first; the slots' sources then lie in LDS, in
+// the keys' place, and every array is read through them and written in slot
+// order, one array after the other: the reads of one array stay within the L1,
+// and the writes are whole lines.  (The particles written to their slots
+// from registers, all arrays at once, filled lines of all arrays piecemeal, and
+// more groups per CU only drove them out of the L2 earlier, 638 -> 888 us.)
+// Two groups of 16 waves fill a CU within 64 registers per thread: cell
+// and rank share one, two keys another, and the batches are as large as still
+// fits without scratch (in groups of 512 the items' 32 registers do not).
+// 19M particles in mixed precision 638 -> 477 us, 0.87M in FP64 48 -> 44 us.
 template <class P, int DIM>
-__global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename P::Real> A) {
+__global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
   if (!A.st->sort_request) return;
   extern __shared__ __align__(16) int sm[];
@@ -312,7 +322,10 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
   unsigned short* keys = first + TC;                            // kArrangeCap: keys by cell
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int nwave = kArrangeBlock / 64;
-  constexpr int U = kArrangeItems, V = 4;
+  constexpr unsigned kCellBits = 11, kCellMask = (1u << kCellBits) - 1u;
+  static_assert(kArrangeOrderCells <= (1 << kCellBits) && (long long)kArrangeCap << kCellBits <= 1ll << 32);
+  // items in flight: in the ranking pass, in the moves
+  constexpr int U = kArrangeItems, V = P::kAbs ? 1 : 2, W = (P::kAbs || DIM == 2) ? 4 : 2;
   const PBuf<Real> S = A.buf[1];
   const PBuf<Real> D = A.buf[0];
   const unsigned long long below = (1ull << lane) - 1ull;
@@ -338,7 +351,8 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
     if (tid == 0) cmax_s = 0;
     __syncthreads();
     // rank of each particle within its cell, in arrival order
-    int cell_of[U], rank_of[U];
+    unsigned place[U];      // cell | rank << kCellBits
+    unsigned key2[U / 2];   // the keys of two particles
     if (ordered) {
 #pragma unroll
       for (int u0 = 0; u0 < U; u0 += V) {
@@ -368,9 +382,11 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
           }
           const int cl = cell_index<P, DIM>(c, org, A.tile);
           const unsigned k = order_key<P, DIM>(x[v][0], x[v][1]);
-          rank_of[u0 + v] = 0;
-          if (tid + (u0 + v) * kArrangeBlock < n) rank_of[u0 + v] = atomicAdd(&cnt[cl], 1);
-          cell_of[u0 + v] = cl | (int)(k << 16);
+          unsigned r = 0;
+          if (tid + (u0 + v) * kArrangeBlock < n) r = (unsigned)atomicAdd(&cnt[cl], 1);
+          place[u0 + v] = (unsigned)cl | (r << kCellBits);
+          if (((u0 + v) & 1) == 0) key2[(u0 + v) / 2] = k;
+          else key2[(u0 + v) / 2] |= k << 16;
         }
       }
     } else {
@@ -421,7 +437,7 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
 #pragma unroll
       for (int u = 0; u < U; ++u)
         if (tid + u * kArrangeBlock < n)
-          keys[first[cell_of[u] & 0xffff] + rank_of[u]] = (unsigned short)((unsigned)cell_of[u] >> 16);
+          keys[first[place[u] & kCellMask] + (place[u] >> kCellBits)] = (unsigned short)(key2[u / 2] >> (16 * (u & 1)));
     }
     __syncthreads();
     float mb[3] = {0.0f, 0.0f, 0.0f};
@@ -437,48 +453,55 @@ __global__ void __launch_bounds__(kArrangeBlock) sort_arrange(SortArgs<typename 
     };
     if (ordered) {
 #pragma unroll
-      for (int u0 = 0; u0 < U; u0 += V) {
-        if (u0 * kArrangeBlock >= n) break;
-        int pc[V], tag[V], slot[V];
-        Real x[V][3], uu[V][3];
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          const int q = s0 + min(tid + (u0 + v) * kArrangeBlock, n - 1);
-          pc[v] = P::kAbs ? 0 : S.cell[q];
-#pragma unroll
-          for (int d = 0; d < DIM; ++d) x[v][d] = S.pos[d][q];
-#pragma unroll
-          for (int d = 0; d < 3; ++d) uu[v][d] = S.u[d][q];
-          tag[v] = S.tag[q];
-        }
-#pragma unroll
-        for (int v = 0; v < V; ++v) {
-          // the rank in the order of the keys (equal keys in arrival order);
-          // a cell too dense for a look at all its keys keeps the arrival order
-          const int cl = cell_of[u0 + v] & 0xffff, m = cnt[cl], f0 = first[cl];
-          const int kv = (int)((unsigned)cell_of[u0 + v] >> 16);
-          int k = rank_of[u0 + v];
-          if (m <= kArrangeOrderCount) {
-            const int r = k;
-            k = 0;
-            for (int j = 0; j < m; ++j) {
-              const int o = keys[f0 + j];
-              k += (o < kv || (o == kv && j < r)) ? 1 : 0;
-            }
+      for (int u = 0; u < U; ++u) {
+        if (u * kArrangeBlock >= n) break;
+        if (tid + u * kArrangeBlock >= n) continue;
+        // the rank in the order of the keys (equal keys in arrival order);
+        // a cell too dense for a look at all its keys keeps the arrival order
+        const int cl = (int)(place[u] & kCellMask), m = cnt[cl], f0 = first[cl];
+        int k = (int)(place[u] >> kCellBits);
+        if (m <= kArrangeOrderCount) {
+          const int r = k, kv = keys[f0 + r];
+          k = 0;
+          for (int j = 0; j < m; ++j) {
+            const int o = keys[f0 + j];
+            k += (o < kv || (o == kv && j < r)) ? 1 : 0;
           }
-          slot[v] = slot_of(cl, k);
         }
+        place[u] = (unsigned)slot_of(cl, k);
+      }
+      // the source of every slot, in the keys' place
+      __syncthreads();
 #pragma unroll
-        for (int v = 0; v < V; ++v) {
-          if (tid + (u0 + v) * kArrangeBlock >= n) continue;
-          if (!P::kAbs) bound((float)uu[v][0], (float)uu[v][1], (float)uu[v][2]);
-          const int o = s0 + slot[v];
-          if (!P::kAbs) D.cell[o] = pc[v];
+      for (int u = 0; u < U; ++u)
+        if (tid + u * kArrangeBlock < n) keys[place[u]] = (unsigned short)(tid + u * kArrangeBlock);
+      __syncthreads();
+#pragma unroll 1
+      for (int u0 = 0; u0 < U; u0 += W) {
+        if (u0 * kArrangeBlock >= n) break;
+        int src[W];
+        const int o0 = tid + u0 * kArrangeBlock;
 #pragma unroll
-          for (int d = 0; d < DIM; ++d) D.pos[d][o] = x[v][d];
+        for (int u = 0; u < W; ++u) src[u] = s0 + keys[min(o0 + u * kArrangeBlock, n - 1)];
+        auto move = [&](const auto* from, auto* to, auto* v) {
 #pragma unroll
-          for (int d = 0; d < 3; ++d) D.u[d][o] = uu[v][d];
-          D.tag[o] = tag[v];
+          for (int u = 0; u < W; ++u) v[u] = from[src[u]];
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+            if (o0 + u * kArrangeBlock < n) to[s0 + o0 + u * kArrangeBlock] = v[u];
+        };
+        int iv[W];
+        Real rv[W], uv[3][W];
+        if (!P::kAbs) move(S.cell, D.cell, iv);
+        move(S.tag, D.tag, iv);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) move(S.pos[d], D.pos[d], rv);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) move(S.u[d], D.u[d], uv[d]);
+        if (!P::kAbs) {
+#pragma unroll
+          for (int u = 0; u < W; ++u)
+            if (o0 + u * kArrangeBlock < n) bound((float)uv[0][u], (float)uv[1][u], (float)uv[2][u]);
         }
       }
     } else {
