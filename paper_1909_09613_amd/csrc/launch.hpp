@@ -26,13 +26,12 @@ struct SortArgs {
   int tile[3];
   int tc;             // cells of a full tile
   int kcap;           // ranks within a cell ordered level by level (arrange pass)
-  int* counts;        // nkeys
-  int* cursor;        // nkeys
+  int* counts;        // nkeys: particles per segment (zero between sorts)
   int* seg;           // nkeys + 1
   int* keys;          // np_total
   int* bbox;          // 6 G
   float* jb;          // 4 G: per-tile current bounds and cell counts, set from the sorted particles
-  const int* tile_run;
+  const int2* tiles;  // G: first cell (packed) and run
 };
 
 // Block size, particles per thread and largest grid of the sort's count and

@@ -59,7 +59,7 @@ struct Layout {
   size_t p_cell[2], p_pos[2][3], p_u[2][3], p_tag[2];
   // fields / current: component-major
   // scratch
-  size_t s_state, s_runs, s_tile_run, s_tiles, s_counts, s_cursor, s_seg, s_bbox, s_jb, s_keys, s_blk_run, s_blk_first, s_acc,
+  size_t s_state, s_runs, s_tiles, s_counts, s_seg, s_bbox, s_jb, s_keys, s_blk_run, s_blk_first, s_acc,
       s_part, s_rho, s_coarse;
   size_t coarse_bytes;
   long long gmax;
@@ -173,13 +173,9 @@ Layout make_layout(const pic_run_desc* runs, int n_runs) {
   off += align_up(sizeof(DevState));
   L.s_runs = off;
   off += align_up((f64 ? sizeof(RunDev<double>) : sizeof(RunDev<float>)) * n_runs);
-  L.s_tile_run = off;
-  off += align_up(4 * gmax);
   L.s_tiles = off;
-  off += align_up(sizeof(int4) * gmax);
+  off += align_up(sizeof(int2) * gmax);
   L.s_counts = off;
-  off += align_up(4 * 2 * gmax);
-  L.s_cursor = off;
   off += align_up(4 * 2 * gmax);
   L.s_seg = off;
   off += align_up(4 * (2 * gmax + 1));
@@ -246,8 +242,7 @@ struct pic_ctx {
   // step between two stream events
   hipGraphExec_t gexec_gpd = nullptr;
   hipGraph_t graph_gpd = nullptr;
-  std::vector<int> tile_run_host;
-  std::vector<int4> tiles_host;
+  std::vector<int2> tiles_host;
   std::vector<int> blk_run_host, blk_first_host;
   // called by pic_destroy once the stream has drained (allocation-free
   // initialisation: releases the device's static scratch)
@@ -500,22 +495,19 @@ pic_status apply_tiling(pic_ctx* c) {
     c->groups_skip = std::min(kMaxGroups, c->cus * gpd_groups_per_cu<Pol>(c->order, nd, c->lds, true));
   }
   // device tables
-  c->tile_run_host.assign(G, 0);
-  c->tiles_host.assign(G, int4{0, 0, 0, 0});
+  c->tiles_host.assign(G, int2{0, 0});
   for (int r = 0; r < c->nruns; ++r) {
     const RunHost& H = c->runs[r];
     for (int t = 0; t < H.ntiles; ++t) {
-      c->tile_run_host[H.tile0 + t] = r;
-      c->tiles_host[H.tile0 + t] = {t % H.ntile[0] * c->tile[0], t / H.ntile[0] % H.ntile[1] * c->tile[1],
-                                    nd == 3 ? t / (H.ntile[0] * H.ntile[1]) * c->tile[2] : 0, r};
+      const int x = t % H.ntile[0] * c->tile[0], y = t / H.ntile[0] % H.ntile[1] * c->tile[1];
+      const int z = nd == 3 ? t / (H.ntile[0] * H.ntile[1]) * c->tile[2] : 0;
+      c->tiles_host[H.tile0 + t] = {nd == 2 ? pack_cell<2>(x, y, 0) : pack_cell<3>(x, y, z), r};
     }
   }
   hipError_t e = host_copy(c, c->S + c->lay.s_runs, rd.data(), sizeof(RunDev<Real>) * rd.size(),
                                 hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = host_copy(c, c->S + c->lay.s_tile_run, c->tile_run_host.data(), 4 * G, hipMemcpyHostToDevice);
-  if (e == hipSuccess)
-    e = host_copy(c, c->S + c->lay.s_tiles, c->tiles_host.data(), sizeof(int4) * G, hipMemcpyHostToDevice);
+    e = host_copy(c, c->S + c->lay.s_tiles, c->tiles_host.data(), sizeof(int2) * G, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   return c->hip(e, "apply_tiling");
 }
@@ -538,7 +530,7 @@ pic_status upload_static(pic_ctx* c) {
   if (e == hipSuccess) e = hipMemsetAsync(c->J, 0, c->lay.bytes[2], c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->P, 0, c->lay.bytes[0], c->stream);
   if (e == hipSuccess) e = hipMemsetAsync(c->S + c->lay.s_state, 0, sizeof(DevState), c->stream);
-  // the sort keeps its counts and cursors zero between sorts, the particle
+  // the sort keeps its counts zero between sorts, the particle
   // kernel its global coarse windows
   if (e == hipSuccess) e = hipMemsetAsync(c->S + c->lay.s_counts, 0, c->lay.s_seg - c->lay.s_counts, c->stream);
   if (e == hipSuccess && c->lay.coarse_bytes)
@@ -551,7 +543,7 @@ template <class Real>
 GpdArgs<Real> gpd_args(pic_ctx* c) {
   GpdArgs<Real> a{};
   a.runs = reinterpret_cast<const RunDev<Real>*>(c->S + c->lay.s_runs);
-  a.tiles = reinterpret_cast<const int4*>(c->S + c->lay.s_tiles);
+  a.tiles = reinterpret_cast<const int2*>(c->S + c->lay.s_tiles);
   a.seg = reinterpret_cast<const int*>(c->S + c->lay.s_seg);
   a.bbox = reinterpret_cast<int*>(c->S + c->lay.s_bbox);
   a.jb = reinterpret_cast<float*>(c->S + c->lay.s_jb);
@@ -595,12 +587,11 @@ SortArgs<Real> sort_args(pic_ctx* c) {
   a.tc = c->tile[0] * c->tile[1] * c->tile[2];
   a.kcap = arrange_kcap(a.tc);
   a.counts = reinterpret_cast<int*>(c->S + c->lay.s_counts);
-  a.cursor = reinterpret_cast<int*>(c->S + c->lay.s_cursor);
   a.seg = reinterpret_cast<int*>(c->S + c->lay.s_seg);
   a.keys = reinterpret_cast<int*>(c->S + c->lay.s_keys);
   a.bbox = reinterpret_cast<int*>(c->S + c->lay.s_bbox);
   a.jb = reinterpret_cast<float*>(c->S + c->lay.s_jb);
-  a.tile_run = reinterpret_cast<const int*>(c->S + c->lay.s_tile_run);
+  a.tiles = reinterpret_cast<const int2*>(c->S + c->lay.s_tiles);
   return a;
 }
 

@@ -4,9 +4,9 @@
 //
 // count    key = 2 * tile + species per particle; wave-aggregated counts;
 //          the last block to finish scans the counts into segment offsets
-//          (clearing the counts for the next sort) and resets every tile's
-//          box to its rectangle
-// scatter  each particle to its segment of the other store
+//          and clears them
+// scatter  each particle to its segment of the other store (the counts again
+//          count what each segment holds), every tile's box to its rectangle
 // arrange  one block per segment: order the segment back into the current
 //          store by (rank within its cell, cell): first every cell's first
 //          particle, cells in tile order, then every cell's second particle,
@@ -15,8 +15,8 @@
 //          atomics of a wave touch distinct, nearly consecutive LDS
 //          addresses.  Ranks beyond `kcap` (dense cells) follow in cell order.
 //          The last arrange block to finish clears the request and counts
-//          the sort.  Between sorts the counts and cursors are zero, so a
-//          sort needs no clearing pass, and each of the three kernels reads
+//          the sort.  Between sorts the counts are zero, so a sort needs no
+//          clearing pass, and each of the three kernels reads
 //          the request flag itself (only the particle kernel sets it, and it
 //          does not run during a sort).
 #include "common.hpp"
@@ -35,15 +35,6 @@ __device__ int find_run(const RunDev<Real>* runs, int nruns, long long p) {
     else hi = mid - 1;
   }
   return lo;
-}
-
-// The run of particle p of a wave that holds particles p0..p1 (a wave lies in
-// one run but for the few at a run's end).
-template <class Real>
-__device__ __forceinline__ int run_of(const RunDev<Real>* runs, int nruns, long long p, long long p0, long long p1) {
-  if (nruns == 1) return 0;
-  const int r0 = find_run(runs, nruns, p0);
-  return (r0 == nruns - 1 || p1 < runs[r0 + 1].p0) ? r0 : find_run(runs, nruns, p);
 }
 
 // The valid lanes of the wave that share this lane's key.
@@ -65,50 +56,46 @@ __device__ __forceinline__ int tile_of(int m, float inv) { return (int)(((float)
 
 }  // namespace
 
-// Exclusive scan of the counts into segment offsets by one block (clearing
-// the counts for the next sort), and every tile's box reset to its
-// rectangle.  The counts were added with device-scope atomics; they are read
-// the same way.
+// Exclusive scan of the counts into segment offsets by one block, which leaves
+// the counts zero for the scatter.  The counts were added with device-scope
+// atomics; they are read the same way, several per thread in flight (one after
+// the other, the 4700 of 24 runs took a tenth of the whole pass).
 template <class Real>
-__device__ void scan_counts(const SortArgs<Real>& A, long long* part) {
-  const int tid = threadIdx.x, nth = blockDim.x;
-  const int chunk = (A.nkeys + nth - 1) / nth;
-  const int lo = tid * chunk;
-  const int hi = min(lo + chunk, A.nkeys);
-  long long s = 0;
-  for (int i = lo; i < hi; ++i) s += __hip_atomic_load(&A.counts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  part[tid] = s;
-  __syncthreads();
-  for (int off = 1; off < nth; off <<= 1) {
-    const long long v = (tid >= off) ? part[tid - off] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
-  }
-  long long base = part[tid] - s;  // exclusive
-  for (int i = lo; i < hi; ++i) {
-    const int c = __hip_atomic_load(&A.counts[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    A.seg[i] = (int)base;
-    base += c;
-    A.counts[i] = 0;
-  }
-  if (tid == nth - 1) A.seg[A.nkeys] = (int)part[nth - 1];
-  // every tile's particles now lie in its rectangle; its current bounds are
-  // rebuilt by the arrange pass
-  for (int i = tid; i < 4 * A.G; i += nth) A.jb[i] = 0.0f;
-  for (int g = tid; g < A.G; g += nth) {
-    const RunDev<Real>& R = A.runs[A.tile_run[g]];
-    const int lt = g - R.tile0;
-    int tc[3];
-    tc[0] = lt % R.ntile[0];
-    tc[1] = (lt / R.ntile[0]) % R.ntile[1];
-    tc[2] = lt / (R.ntile[0] * R.ntile[1]);
-    for (int d = 0; d < 3; ++d) {
-      const int org = tc[d] * A.tile[d];
-      A.bbox[g * 6 + 2 * d] = 0;
-      A.bbox[g * 6 + 2 * d + 1] = min(A.tile[d], R.n[d] - org) - 1;
+__device__ void scan_counts(const SortArgs<Real>& A, int* part) {
+  constexpr int K = 8;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int done = 0;
+  for (int i0 = 0; i0 < A.nkeys; i0 += K * kSortBlock) {
+    const int lo = i0 + K * tid;
+    int c[K], s = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+      c[k] = lo + k < A.nkeys ? __hip_atomic_load(&A.counts[lo + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k) s += c[k];
+    int incl = s;
+    for (int off = 1; off < 64; off <<= 1) {
+      const int t = __shfl_up(incl, off);
+      if (lane >= off) incl += t;
     }
+    if (lane == 63) part[wave] = incl;
+    __syncthreads();
+    int base = done + incl - s;
+#pragma unroll
+    for (int w = 0; w < kSortBlock / 64; ++w) {
+      if (w < wave) base += part[w];
+      done += part[w];
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+      if (lo + k >= A.nkeys) break;
+      A.seg[lo + k] = base;
+      base += c[k];
+      A.counts[lo + k] = 0;
+    }
+    __syncthreads();
   }
+  if (tid == 0) A.seg[A.nkeys] = done;
 }
 
 // Count and scatter take kSortItems particles per thread at once, so that a
@@ -116,7 +103,7 @@ __device__ void scan_counts(const SortArgs<Real>& A, long long* part) {
 // per distinct key of the wave, all keys in one instruction.  (One particle
 // per thread and an atomic round trip per distinct key, one after the other:
 // 19M particles in mixed precision 311 and 404 us, 0.87M in FP64 56 and 48 us;
-// now 191 and 325, 26 and 20 us.)
+// now 180 and 322, 23 and 20 us.)
 template <class P, int DIM>
 __global__ void __launch_bounds__(kSortBlock) sort_count(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
@@ -141,14 +128,14 @@ __global__ void __launch_bounds__(kSortBlock) sort_count(SortArgs<typename P::Re
         pc[v] = B.cell[p];
       }
     }
-#pragma unroll
-    for (int v = 0; v < V; ++v) {
+    // the group's particles lie in one run but at a run's end
+    const int r0 = A.nruns == 1 ? 0 : find_run(A.runs, A.nruns, b0);
+    const bool one = r0 == A.nruns - 1 || b0 + kSortBlock * V <= A.runs[r0 + 1].p0;
+    auto count_in = [&](int v, const RunDev<Real>& R) {
       const long long p = b0 + v * kSortBlock + threadIdx.x;
       const bool valid = p < A.np_total;
       int key = 0;
       if (valid) {
-        const long long w0 = p - (threadIdx.x & 63);
-        const RunDev<Real>& R = A.runs[run_of(A.runs, A.nruns, p, w0, min(w0 + 63, A.np_total - 1))];
         int c[3] = {0, 0, 0};
         if (P::kAbs) {
 #pragma unroll
@@ -172,10 +159,18 @@ __global__ void __launch_bounds__(kSortBlock) sort_count(SortArgs<typename P::Re
       }
       const unsigned long long m = same_key(key, valid);
       if (m && __ffsll((long long)m) - 1 == (int)(threadIdx.x & 63)) atomicAdd(A.counts + key, __popcll(m));
+    };
+    if (one) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) count_in(v, A.runs[r0]);
+    } else {
+#pragma unroll
+      for (int v = 0; v < V; ++v)
+        count_in(v, A.runs[find_run(A.runs, A.nruns, min(b0 + v * kSortBlock + threadIdx.x, A.np_total - 1))]);
     }
   }
   // the last block to finish turns the counts into segment offsets
-  __shared__ long long part[kSortBlock];
+  __shared__ int part[kSortBlock / 64];
   __shared__ int last;
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -198,6 +193,19 @@ __global__ void __launch_bounds__(kSortBlock) sort_scatter(SortArgs<typename P::
   const PBuf<Real> D = A.buf[1];
   const int lane = threadIdx.x & 63;
   const long long stride = (long long)gridDim.x * kSortBlock * V;
+  // every tile's particles now lie in its rectangle; its current bounds are
+  // rebuilt by the arrange pass
+  for (int g = blockIdx.x * kSortBlock + threadIdx.x; g < A.G; g += gridDim.x * kSortBlock) {
+    const int2 where = A.tiles[g];
+    int org[3];
+    unpack_cell<DIM>(where.x, org[0], org[1], org[2]);
+    const RunDev<Real>& R = A.runs[where.y];
+    for (int d = 0; d < 3; ++d) {
+      A.bbox[g * 6 + 2 * d] = 0;
+      A.bbox[g * 6 + 2 * d + 1] = min(A.tile[d], R.n[d] - org[d]) - 1;
+    }
+    for (int c = 0; c < 4; ++c) A.jb[4 * g + c] = 0.0f;
+  }
   for (long long b0 = (long long)blockIdx.x * kSortBlock * V; b0 < A.np_total; b0 += stride) {
     int key[V], pc[V], tag[V], to[V];
     Real x[V][3], u[V][3];
@@ -218,7 +226,7 @@ __global__ void __launch_bounds__(kSortBlock) sort_scatter(SortArgs<typename P::
       m[v] = same_key(key[v], b0 + v * kSortBlock + threadIdx.x < A.np_total);
       to[v] = 0;
       if (m[v] && __ffsll((long long)m[v]) - 1 == lane)
-        to[v] = A.seg[key[v]] + atomicAdd(A.cursor + key[v], __popcll(m[v]));
+        to[v] = A.seg[key[v]] + atomicAdd(A.counts + key[v], __popcll(m[v]));
     }
 #pragma unroll
     for (int v = 0; v < V; ++v) {
@@ -329,19 +337,17 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
   const PBuf<Real> S = A.buf[1];
   const PBuf<Real> D = A.buf[0];
   const unsigned long long below = (1ull << lane) - 1ull;
-  // the scatter is done with the cursors: clear them for the next sort
-  for (int i = blockIdx.x * kArrangeBlock + tid; i < A.nkeys; i += gridDim.x * kArrangeBlock) A.cursor[i] = 0;
+  // the scatter is done with the counts: clear them for the next sort
+  for (int i = blockIdx.x * kArrangeBlock + tid; i < A.nkeys; i += gridDim.x * kArrangeBlock) A.counts[i] = 0;
   for (int key = blockIdx.x; key < A.nkeys; key += gridDim.x) {
     const int s0 = A.seg[key];
     const int n = A.seg[key + 1] - s0;
     if (n == 0) continue;
     const int g = key >> 1;
-    const RunDev<Real>& R = A.runs[A.tile_run[g]];
-    const int lt = g - R.tile0;
+    const int2 where = A.tiles[g];
+    const RunDev<Real>& R = A.runs[where.y];
     int org[3];
-    org[0] = (lt % R.ntile[0]) * A.tile[0];
-    org[1] = ((lt / R.ntile[0]) % R.ntile[1]) * A.tile[1];
-    org[2] = (DIM == 3) ? (lt / (R.ntile[0] * R.ntile[1])) * A.tile[2] : 0;
+    unpack_cell<DIM>(where.x, org[0], org[1], org[2]);
     // a segment of up to kArrangeCap particles keeps each particle's cell and
     // rank in registers and orders the cells; a larger one (dense cells, or
     // more particles per cell than any workload here has) takes the arrival
