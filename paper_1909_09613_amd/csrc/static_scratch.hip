@@ -9,6 +9,7 @@
 // and only that address is handed to the context.  One array per device, so
 // at most one such context may be alive per device at a time; a second one
 // is refused until the first is destroyed.
+#include <algorithm>
 #include <cstdio>
 #include <mutex>
 
@@ -17,7 +18,10 @@
 
 namespace {
 
-constexpr size_t kStaticScratchBytes = size_t(64) << 20;  // 64 MiB per device
+// 64 MiB per device, and next to them the T_l factors of the runs' tables (at
+// most 144 bytes of a run's two kilobytes)
+constexpr size_t kStaticLimit = size_t(64) << 20;
+constexpr size_t kStaticScratchBytes = kStaticLimit + (size_t(8) << 20);
 constexpr int kMaxDevices = 64;
 
 std::mutex g_mu;
@@ -42,10 +46,12 @@ extern "C" pic_status pic_init_static(const pic_run_desc* runs, int32_t n_runs, 
   size_t need[4] = {0, 0, 0, 0};
   pic_status st = pic_query_layout(runs, n_runs, need);
   if (st != PIC_OK) return st;
-  if (need[3] > kStaticScratchBytes) {
+  const size_t factors =
+      (size_t)n_runs * 3 * (runs[0].precision == PIC_FP64 ? sizeof(wtpic::TFac<double>) : sizeof(wtpic::TFac<float>));
+  if (need[3] > std::min(kStaticScratchBytes, kStaticLimit + factors)) {
     char msg[200];
     snprintf(msg, sizeof msg, "these runs need %zu bytes of scratch; the static scratch holds %zu", need[3],
-             kStaticScratchBytes);
+             kStaticLimit);
     wtpic::set_global_error(msg);
     return PIC_ERR_ARG;
   }
