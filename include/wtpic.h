@@ -138,10 +138,10 @@ pic_status pic_init(const pic_run_desc *runs, int32_t n_runs, const pic_buffers 
  * context of this call may be alive per device: a second call on a device
  * whose array is in use returns PIC_ERR_STATE until the first context is
  * destroyed.  Runs whose scratch (pic_query_layout, bytes_out[3]) exceeds
- * 64 MiB, and 144 bytes a run (FP64; 72 in mixed precision), are refused with
- * PIC_ERR_ARG (e.g. 3D mixed precision, whose coarse current windows alone take
- * 335 MB; 2D runs of up to about 14M particles
- * fit).  Otherwise as pic_init. */
+ * 64 MiB, not counting 144 bytes a run (FP64; 72 in mixed precision) and 12 for
+ * every 4 x 4 (2D) or 2 x 2 x 2 (3D) cells, are refused with PIC_ERR_ARG
+ * (e.g. 3D mixed precision, whose coarse current windows alone take 335 MB;
+ * 2D runs of up to about 14M particles fit).  Otherwise as pic_init. */
 pic_status pic_init_static(const pic_run_desc *runs, int32_t n_runs, const pic_buffers *bufs,
                            void *hip_stream, pic_ctx **out);
 

@@ -156,7 +156,7 @@ struct TileState {
 template <class Real>
 struct GpdArgs {
   const RunDev<Real>* runs;
-  const int2* tiles;     // per tile: first cell (packed) and run
+  const int4* tiles;     // per tile: first cell (x, y, z) and run
   const int* seg;        // 2G+1 segment offsets: key 2g+s covers [seg[key], seg[key+1])
   int* bbox;             // per tile: lo0, hi0, lo1, hi1, lo2, hi2 (cells, tile-relative)
   float* jb;             // per tile: bounds of the current contributions and cell counts (gpd.hip)

@@ -424,7 +424,7 @@ struct GpdShape {
 
 template <class P, int L, int DIM, int KT, bool SKIP, int CP>
 __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, const RunDev<typename P::Real>& R,
-                                         const int2 where, const TileState ts, const int g, unsigned char* lds,
+                                         const int4 where, const TileState ts, const int g, unsigned char* lds,
                                          int* sred, typename P::Real* spc) {
   using Real = typename P::Real;
   using Acc = typename P::Acc;
@@ -438,8 +438,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
   const int tid = threadIdx.x;
   const int nth = GpdShape<L, DIM, SKIP>::kBlock;
 
-  int org[3];
-  unpack_cell<DIM>(where.x, org[0], org[1], org[2]);
+  const int org[3] = {where.x, where.y, where.z};
   const int* bb = ts.bb;
   int fo[3] = {0, 0, 0}, fs[3] = {1, 1, 1}, jo[3] = {0, 0, 0}, jsz[3] = {1, 1, 1};
   bool fits = true;
@@ -1393,16 +1392,16 @@ template <class P, int L, int DIM, bool SKIP, int CP>
 __global__ void __launch_bounds__((GpdShape<L, DIM, SKIP>::kBlock))
 __attribute__((amdgpu_waves_per_eu(GpdShape<L, DIM, SKIP>::kWaves)))
     gpd_kernel(GpdArgs<typename P::Real> A, const RunDev<typename P::Real>* __restrict__ runs,
-               const int2* __restrict__ tiles) {
+               const int4* __restrict__ tiles) {
   extern __shared__ __align__(16) unsigned char lds_dyn[];
   __shared__ int sred[13];
   __shared__ int next;
   __shared__ __align__(32) typename P::Real spc[8];   // per-species constants of the tile's run
   const bool queue = A.G > (int)gridDim.x;
   for (int g = blockIdx.x; g < A.G;) {
-    const int2 where = tiles[g];
+    const int4 where = tiles[g];
     const TileState ts = load_tile(A, g);
-    const RunDev<typename P::Real>& R = runs[where.y];
+    const RunDev<typename P::Real>& R = runs[where.w];
     if (R.KT == L + 1)
       gpd_tile<P, L, DIM, L + 1, SKIP, CP>(A, R, where, ts, g, lds_dyn, sred, spc);
     else

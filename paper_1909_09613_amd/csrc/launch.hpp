@@ -12,6 +12,10 @@ namespace wtpic {
 // a function pic_destroy calls with arg once the context's stream has
 // drained, and the text pic_last_error(NULL) returns.
 void set_destroy_hook(pic_ctx* c, void (*hook)(int), int arg);
+// Scratch of these runs that the limit of the static scratch leaves out: the
+// T_l factors with their tables and the tiles' first cells (of the smallest
+// tiles).
+size_t static_allowance(const pic_run_desc* runs, int n_runs);
 void set_global_error(const char* msg);
 
 template <class Real>
@@ -31,7 +35,7 @@ struct SortArgs {
   int* keys;          // np_total
   int* bbox;          // 6 G
   float* jb;          // 4 G: per-tile current bounds and cell counts, set from the sorted particles
-  const int2* tiles;  // G: first cell (packed) and run
+  const int4* tiles;  // G: first cell (x, y, z) and run
 };
 
 // Block size, particles per thread and largest grid of the sort's count and

@@ -174,7 +174,7 @@ Layout make_layout(const pic_run_desc* runs, int n_runs) {
   L.s_runs = off;
   off += align_up((f64 ? sizeof(RunDev<double>) : sizeof(RunDev<float>)) * n_runs);
   L.s_tiles = off;
-  off += align_up(sizeof(int2) * gmax);
+  off += align_up(sizeof(int4) * gmax);
   L.s_counts = off;
   off += align_up(4 * 2 * gmax);
   L.s_seg = off;
@@ -242,7 +242,7 @@ struct pic_ctx {
   // step between two stream events
   hipGraphExec_t gexec_gpd = nullptr;
   hipGraph_t graph_gpd = nullptr;
-  std::vector<int2> tiles_host;
+  std::vector<int4> tiles_host;
   std::vector<int> blk_run_host, blk_first_host;
   // called by pic_destroy once the stream has drained (allocation-free
   // initialisation: releases the device's static scratch)
@@ -495,19 +495,19 @@ pic_status apply_tiling(pic_ctx* c) {
     c->groups_skip = std::min(kMaxGroups, c->cus * gpd_groups_per_cu<Pol>(c->order, nd, c->lds, true));
   }
   // device tables
-  c->tiles_host.assign(G, int2{0, 0});
+  c->tiles_host.assign(G, int4{0, 0, 0, 0});
   for (int r = 0; r < c->nruns; ++r) {
     const RunHost& H = c->runs[r];
     for (int t = 0; t < H.ntiles; ++t) {
       const int x = t % H.ntile[0] * c->tile[0], y = t / H.ntile[0] % H.ntile[1] * c->tile[1];
       const int z = nd == 3 ? t / (H.ntile[0] * H.ntile[1]) * c->tile[2] : 0;
-      c->tiles_host[H.tile0 + t] = {nd == 2 ? pack_cell<2>(x, y, 0) : pack_cell<3>(x, y, z), r};
+      c->tiles_host[H.tile0 + t] = {x, y, z, r};
     }
   }
   hipError_t e = host_copy(c, c->S + c->lay.s_runs, rd.data(), sizeof(RunDev<Real>) * rd.size(),
                                 hipMemcpyHostToDevice);
   if (e == hipSuccess)
-    e = host_copy(c, c->S + c->lay.s_tiles, c->tiles_host.data(), sizeof(int2) * G, hipMemcpyHostToDevice);
+    e = host_copy(c, c->S + c->lay.s_tiles, c->tiles_host.data(), sizeof(int4) * G, hipMemcpyHostToDevice);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   return c->hip(e, "apply_tiling");
 }
@@ -543,7 +543,7 @@ template <class Real>
 GpdArgs<Real> gpd_args(pic_ctx* c) {
   GpdArgs<Real> a{};
   a.runs = reinterpret_cast<const RunDev<Real>*>(c->S + c->lay.s_runs);
-  a.tiles = reinterpret_cast<const int2*>(c->S + c->lay.s_tiles);
+  a.tiles = reinterpret_cast<const int4*>(c->S + c->lay.s_tiles);
   a.seg = reinterpret_cast<const int*>(c->S + c->lay.s_seg);
   a.bbox = reinterpret_cast<int*>(c->S + c->lay.s_bbox);
   a.jb = reinterpret_cast<float*>(c->S + c->lay.s_jb);
@@ -591,7 +591,7 @@ SortArgs<Real> sort_args(pic_ctx* c) {
   a.keys = reinterpret_cast<int*>(c->S + c->lay.s_keys);
   a.bbox = reinterpret_cast<int*>(c->S + c->lay.s_bbox);
   a.jb = reinterpret_cast<float*>(c->S + c->lay.s_jb);
-  a.tiles = reinterpret_cast<const int2*>(c->S + c->lay.s_tiles);
+  a.tiles = reinterpret_cast<const int4*>(c->S + c->lay.s_tiles);
   return a;
 }
 
@@ -886,6 +886,11 @@ void set_destroy_hook(pic_ctx* c, void (*hook)(int), int arg) {
 }
 
 void set_global_error(const char* msg) { g_err = msg; }
+
+size_t static_allowance(const pic_run_desc* runs, int n_runs) {
+  const size_t factors = 3 * (runs[0].precision == PIC_FP64 ? sizeof(TFac<double>) : sizeof(TFac<float>));
+  return factors * n_runs + 12 * (size_t)make_layout(runs, n_runs).gmax;
+}
 
 }  // namespace wtpic
 

@@ -196,10 +196,9 @@ __global__ void __launch_bounds__(kSortBlock) sort_scatter(SortArgs<typename P::
   // every tile's particles now lie in its rectangle; its current bounds are
   // rebuilt by the arrange pass
   for (int g = blockIdx.x * kSortBlock + threadIdx.x; g < A.G; g += gridDim.x * kSortBlock) {
-    const int2 where = A.tiles[g];
-    int org[3];
-    unpack_cell<DIM>(where.x, org[0], org[1], org[2]);
-    const RunDev<Real>& R = A.runs[where.y];
+    const int4 where = A.tiles[g];
+    const int org[3] = {where.x, where.y, where.z};
+    const RunDev<Real>& R = A.runs[where.w];
     for (int d = 0; d < 3; ++d) {
       A.bbox[g * 6 + 2 * d] = 0;
       A.bbox[g * 6 + 2 * d + 1] = min(A.tile[d], R.n[d] - org[d]) - 1;
@@ -313,7 +312,8 @@ __device__ __forceinline__ unsigned order_key(typename P::Real fx, typename P::R
 // more groups per CU only drove them out of the L2 earlier, 638 -> 888 us.)
 // Two groups of 16 waves fill a CU within 64 registers per thread: cell
 // and rank share one, two keys another, and the batches are as large as still
-// fits without scratch (in groups of 512 the items' 32 registers do not).
+// fits without scratch, whose allocation a stream's first launch pays with some
+// 200 us (in groups of 512 the items' 32 registers do not fit).
 // 19M particles in mixed precision 638 -> 477 us, 0.87M in FP64 48 -> 44 us.
 template <class P, int DIM>
 __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typename P::Real> A) {
@@ -340,14 +340,15 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
   // the scatter is done with the counts: clear them for the next sort
   for (int i = blockIdx.x * kArrangeBlock + tid; i < A.nkeys; i += gridDim.x * kArrangeBlock) A.counts[i] = 0;
   for (int key = blockIdx.x; key < A.nkeys; key += gridDim.x) {
-    const int s0 = A.seg[key];
-    const int n = A.seg[key + 1] - s0;
+    // (the group's values in scalar registers: the kernel has no vector one left)
+    const int s0 = __builtin_amdgcn_readfirstlane(A.seg[key]);
+    const int n = __builtin_amdgcn_readfirstlane(A.seg[key + 1]) - s0;
     if (n == 0) continue;
     const int g = key >> 1;
-    const int2 where = A.tiles[g];
-    const RunDev<Real>& R = A.runs[where.y];
-    int org[3];
-    unpack_cell<DIM>(where.x, org[0], org[1], org[2]);
+    const int4 where = A.tiles[g];
+    const RunDev<Real>& R = A.runs[__builtin_amdgcn_readfirstlane(where.w)];
+    const int org[3] = {__builtin_amdgcn_readfirstlane(where.x), __builtin_amdgcn_readfirstlane(where.y),
+                        __builtin_amdgcn_readfirstlane(where.z)};
     // a segment of up to kArrangeCap particles keeps each particle's cell and
     // rank in registers and orders the cells; a larger one (dense cells, or
     // more particles per cell than any workload here has) takes the arrival

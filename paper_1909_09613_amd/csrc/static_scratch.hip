@@ -18,8 +18,8 @@
 
 namespace {
 
-// 64 MiB per device, and next to them the T_l factors of the runs' tables (at
-// most 144 bytes of a run's two kilobytes)
+// 64 MiB per device, and room for what static_allowance leaves out of them (at
+// most 144 bytes of a run's two kilobytes and 12 of a tile's three hundred)
 constexpr size_t kStaticLimit = size_t(64) << 20;
 constexpr size_t kStaticScratchBytes = kStaticLimit + (size_t(8) << 20);
 constexpr int kMaxDevices = 64;
@@ -46,9 +46,7 @@ extern "C" pic_status pic_init_static(const pic_run_desc* runs, int32_t n_runs, 
   size_t need[4] = {0, 0, 0, 0};
   pic_status st = pic_query_layout(runs, n_runs, need);
   if (st != PIC_OK) return st;
-  const size_t factors =
-      (size_t)n_runs * 3 * (runs[0].precision == PIC_FP64 ? sizeof(wtpic::TFac<double>) : sizeof(wtpic::TFac<float>));
-  if (need[3] > std::min(kStaticScratchBytes, kStaticLimit + factors)) {
+  if (need[3] > std::min(kStaticScratchBytes, kStaticLimit + wtpic::static_allowance(runs, n_runs))) {
     char msg[200];
     snprintf(msg, sizeof msg, "these runs need %zu bytes of scratch; the static scratch holds %zu", need[3],
              kStaticLimit);
