@@ -169,14 +169,18 @@ __global__ void __launch_bounds__(kSortBlock) sort_count(SortArgs<typename P::Re
         count_in(v, A.runs[find_run(A.runs, A.nruns, min(b0 + v * kSortBlock + threadIdx.x, A.np_total - 1))]);
     }
   }
-  // the last block to finish turns the counts into segment offsets
+  // the last block to finish turns the counts into segment offsets.  Every wave
+  // waits for its own counts to land before its group takes the ticket: the adds
+  // return nothing, so the barrier does not wait for them, and a fence of thread 0
+  // waits for those of its wave alone.  The counts are touched by device-scope
+  // atomics only, so that having landed is all they need (a fence in every
+  // wave also writes the L2s back: 19M particles in mixed precision 263 us, 118 with
+  // the wait; 7.3M in FP64 205 and 61 us).
   __shared__ int part[kSortBlock / 64];
   __shared__ int last;
+  __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0), the other counters at their maxima
   __syncthreads();
-  if (threadIdx.x == 0) {
-    __threadfence();
-    last = atomicAdd(&A.st->count_done, 1u) == gridDim.x - 1;
-  }
+  if (threadIdx.x == 0) last = atomicAdd(&A.st->count_done, 1u) == gridDim.x - 1;
   __syncthreads();
   if (!last) return;
   __threadfence();
