@@ -545,8 +545,11 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
     }
     __syncthreads();
   }
-  // the last group to finish ends the sort (every group has started and
-  // read the request by then)
+  // the last group to finish ends the sort.  Every wave of a group has read the
+  // request before the group is counted: a group whose segments are all empty
+  // has met no other barrier, and a wave that found the request cleared would
+  // leave its part of the counts to the next sort.
+  __syncthreads();
   if (tid == 0 && atomicAdd(&A.st->arrange_done, 1u) == gridDim.x - 1) {
     A.st->arrange_done = 0;
     A.st->n_sorts += 1;

@@ -4,7 +4,9 @@ kernel is followed (loops included), block by block.
 
 sort_count: the last group to finish reads every group's counts, so no atomic of
 a wave may be on its way when the wave passes the barrier before the group's
-ticket."""
+ticket.  sort_arrange: the last group clears the request that every wave
+reads on entry, so each path to the ticket passes a barrier, also that of a
+group whose segments are all empty."""
 import os
 import re
 import subprocess
@@ -22,7 +24,7 @@ def kernels(tmp_path_factory):
     found, name = {}, None
     for line in out.read_text().splitlines():
         line = line.split(";")[0].strip()
-        m = re.match(r"(_Z\w*sort_count\w*):$", line)
+        m = re.match(r"(_Z\w*sort_(?:count|arrange)\w*):$", line)
         if m:
             name = m.group(1)
             found[name] = []
@@ -76,6 +78,22 @@ def test_counts_have_landed_before_the_ticket(kernels):
             if ln.startswith("s_barrier") and on_the_way:
                 bad.append(ln)
             return on_the_way
+
+        assert any(map(_ticket, kernels[name]))
+        _follow(kernels[name], False, step)
+        assert not bad, name
+
+
+def test_every_wave_has_read_the_request_before_the_ticket(kernels):
+    for name in _of(kernels, "sort_arrange"):
+        bad = []
+
+        def step(ln, passed):
+            if ln.startswith("s_barrier"):
+                return True
+            if _ticket(ln) and not passed:
+                bad.append(ln)
+            return passed
 
         assert any(map(_ticket, kernels[name]))
         _follow(kernels[name], False, step)
