@@ -642,11 +642,12 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
   if (tid >= 6 && tid < 13) sred[tid] = 0;
   __syncthreads();
 
-  // T_l with l + 1 nodes comes from its moments.  With l + 2 it comes from the
-  // run's tables, in 2D FP32 with their leading coefficients in vector
-  // registers, so that the first Horner step of each node reads one scalar
-  // operand (an instruction reads at most one) and needs no copy.
-  constexpr bool kMoments = KT == L + 1;
+  // T_l with l + 1 nodes comes from its moments up to the cubic one.  The
+  // quartic and those with l + 2 nodes come from the run's tables, in 2D FP32 with
+  // their leading coefficients in vector registers, so that the first Horner
+  // step of each node reads one scalar operand (an instruction reads at most
+  // one) and needs no copy.
+  constexpr bool kMoments = KT == L + 1 && L <= 3;
   constexpr bool kTop = !kMoments && kFix && DIM == 2;
   Real ttop[2][KT];
 #pragma unroll
@@ -700,7 +701,7 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
     nn[d] = pin(n);
     qmax[d] = pin(min(rhi - lo, n - 1));
     hoff[d] = pin(kWh.first - fo[d] + lo);
-    toff[d] = pin(R.tf[d].first - fo[d] + lo);
+    toff[d] = pin((kMoments ? R.tf[d].first : R.T[d].first) - fo[d] + lo);
     uoff[d] = pin(kWi.first - jo[d] + lo);
     joff[d] = pin(lo - jo[d]);
   }
@@ -891,9 +892,13 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
       else weights_h(d, R.Wh[d]);
       int b;
       Real gg;
-      split_rt(R.tf[d].sigma, 0, f[d], b, gg);
-      if constexpr (kMoments) tfac_eval<L>(R.tf[d], gg, wt[d]);
-      else tab_eval<L, KT, true>(R.T[d], gg, wt[d], kTop ? ttop[d] : nullptr);
+      if constexpr (kMoments) {
+        tfac_split<L>(R.tf[d], f[d], b, gg);
+        tfac_eval<L>(R.tf[d], gg, wt[d]);
+      } else {
+        split_rt(R.T[d].sigma, 0, f[d], b, gg);
+        tab_eval<L, KT, true>(R.T[d], gg, wt[d], kTop ? ttop[d] : nullptr);
+      }
       it[d] = q[d] + b + toff[d];
     }
 

@@ -374,7 +374,7 @@ pic_status build_runs(pic_ctx* c, std::vector<RunDev<Real>>& out) {
       convert_table(wi, R.Wi[k]);
       convert_table(tt, R.T[k]);
       const TFac<double> tf = make_tfac(l, d.scheme == PIC_WT ? a : 0.5, tt);
-      R.tf[k] = {Real(tf.sigma), Real(tf.kappa), Real(tf.beta), Real(tf.u0), Real(tf.var), tf.first};
+      R.tf[k] = {Real(tf.sigma), Real(tf.a), Real(tf.beta), Real(tf.c), tf.first};
       int lo1, hi1, lo2, hi2, lo3, hi3;
       table_reach(wh, l + 1, lo1, hi1);
       table_reach(tt, KT, lo2, hi2);
@@ -888,7 +888,8 @@ void set_destroy_hook(pic_ctx* c, void (*hook)(int), int arg) {
 void set_global_error(const char* msg) { g_err = msg; }
 
 size_t static_allowance(const pic_run_desc* runs, int n_runs) {
-  const size_t factors = 3 * (runs[0].precision == PIC_FP64 ? sizeof(TFac<double>) : sizeof(TFac<float>));
+  const size_t factors = runs[0].precision == PIC_FP64 ? 144 : 72;
+  static_assert(3 * sizeof(TFac<double>) <= 144 && 3 * sizeof(TFac<float>) <= 72);
   return factors * n_runs + 12 * (size_t)make_layout(runs, n_runs).gmax;
 }
 

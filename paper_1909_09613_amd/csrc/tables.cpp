@@ -142,12 +142,16 @@ TFac<double> make_tfac(int l, double a, const Tab<double>& t) {
   for (int i = 2; i <= l; ++i) fact *= i;
   TFac<double> f;
   f.sigma = t.sigma;
-  f.kappa = (double)(1.0L - 2.0L * a);
-  f.beta = (double)(1.0L / (2.0L * a * fact));
-  // node k lies at first + k from the split's base, the particle at sigma + g
-  f.u0 = (double)(frac(0.5L * l + (long double)a) - t.first - 1);
-  f.var = (double)(l / 12.0L + (long double)a * a / 3.0L);
   f.first = t.first;
+  if ((l & 1) && t.sigma == 0.0) {
+    // a = 1/2, odd l: the table's base is always the particle's cell; counted
+    // from the cell before, the middle of the nodes lies where it does for a < 1/2
+    f.sigma = 1.0;
+    f.first += 1;
+  }
+  f.a = a;
+  f.beta = (double)(1.0L / (2.0L * a * fact));
+  f.c = (double)((long double)a * a / 12.0L);
   return f;
 }
 

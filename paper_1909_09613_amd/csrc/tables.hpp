@@ -30,22 +30,21 @@ struct Tab {
   Real alpha[kMaxNodes];        // coefficient of the knot term
 };
 
-// T_l for c dt <= dx / 2, where it has l + 1 nodes, from its moments: T_l
-// reproduces polynomials of degree l - 1 (its transform, sinc^l(k dx/2)
-// sinc(k c dt), has zeros of order l at the lattice's wave numbers), so that
-// the weights w_k of the nodes at y_k from the particle satisfy
-//     sum w_k y_k^r = (moment r of T_l),  r < l,
-// with variance l/12 + a^2/3 and vanishing odd moments.  These l equations
-// leave one unknown, and the last node's weight is the single power
-// beta max(g - kappa, 0)^l, beta = 1 / (2 a l!), kappa = 1 - 2 a.
+// T_l for c dt <= dx / 2 and l <= 3, where its l + 1 nodes' weights follow from
+// its moments.  T_l reproduces polynomials of degree l - 1 (its transform,
+// sinc^l(k dx/2) sinc(k c dt), has zeros of order l at the lattice's wave
+// numbers), so that with the particle v past the middle of its nodes, v in
+// [a - 1, a], and nodes at y_k from that middle,
+//     sum w_k = 1, sum w_k y_k = v, sum w_k y_k^2 = v^2 + l/12 + a^2/3 (l = 3).
+// These l equations leave one unknown: the outer weight on the side away from
+// the particle is the single power p = beta max(a - |v|, 0)^l.
 template <class Real>
 struct TFac {
-  Real sigma;   // the table's split
-  Real kappa;
-  Real beta;
-  Real u0;      // the particle's distance from node 1 is g + u0
-  Real var;     // l/12 + a^2/3
-  int first;    // the table's first node
+  Real sigma;   // the split: base is the cell before the particle's where f < sigma
+  Real a;       // c dt / dx
+  Real beta;    // 1 / (2 a l!)
+  Real c;       // a^2 / 12
+  int first;    // first node from base
 };
 
 // Split a position given as (cell, in-cell offset f in [0,1)) for a table.
@@ -90,45 +89,53 @@ __host__ __device__ inline void tab_eval(const Tab<Real>& t, Real g, Real* w, co
   }
 }
 
-// Weights w[0..L] of T_l from its moments: the polynomials that the moments
-// give on nodes 0..L-1, plus the last weight times the combination of all
-// nodes that has no moment below L (the L-th difference).  With the node
-// numbers counted from node 1, u is the mean and u^2 + var the second moment.
-// Fewer instructions than the table (14 against 20 for the cubic) and five
-// constants instead of 22 per axis, which the particle loop keeps in scalar
-// registers where it had to load the tables again for every particle.
+// The split of an in-cell offset f for T_l's moments: base from the particle's
+// cell, and v past the middle of the nodes, one rounding of f.
 template <int L, class Real>
-__host__ __device__ inline void tfac_eval(const TFac<Real>& t, Real g, Real* w) {
-  Real d = g - t.kappa;
-  d = d > Real(0) ? d : Real(0);
-  const Real u = g + t.u0;
+__host__ __device__ inline void tfac_split(const TFac<Real>& t, Real f, int& base, Real& v) {
+  constexpr Real mid = L == 2 ? Real(1) : Real(1.5);
+  const bool below = f < t.sigma;
+  base = below ? -1 : 0;
+  v = f - (below ? mid - Real(1) : mid);
+}
+
+// Weights w[0..L], L <= 3, of T_l from its moments, in coordinates about the
+// middle of the nodes: the unknown p is at most a^2/12 (l = 3), so its rounding
+// hardly counts, and the rest are short sums of v.  Root mean square error of a
+// particle's weights against the exact factor, in 2^-24 (FP32; FP64 alike in 2^-53),
+// here / from the table, a = 0.1, 0.3, 0.45, 0.5: linear 0.11 / 2.05, 0.34 / 1.00,
+// 0.49 / 0.80, 0.26 / 0.23; quadratic 0.34 / 0.51, 0.38 / 0.75, 0.40 / 0.76, 0.40 / 0.43;
+// cubic 0.46 / 0.72, 0.44 / 0.58, 0.44 / 0.58, 0.43 / 0.54.  (The quartic's lose
+// more to the cancellation of its cubic terms, 0.63 / 0.47 at a = 0.5: tables.)
+// About as many instructions as the cubic's table (19 against 20), and three
+// constants besides the split where it has 20 per axis, which the particle loop
+// keeps in scalar registers where it had to load the tables again for every
+// particle.
+template <int L, class Real>
+__host__ __device__ inline void tfac_eval(const TFac<Real>& t, Real v, Real* w) {
+  static_assert(L <= 3, "the quartic factor comes from its table");
   if constexpr (L == 1) {
-    w[1] = d * t.beta;
+    w[1] = fmax(fma(v, t.beta, Real(0.5)), Real(0));
     w[0] = Real(1) - w[1];
-  } else if constexpr (L == 2) {
-    const Real p = d * (d * t.beta);
-    w[0] = p - u;
-    w[1] = fma(Real(-2), p, Real(1) + u);
-    w[2] = p;
-  } else if constexpr (L == 3) {
-    const Real p = (d * d) * (d * t.beta);
-    const Real m2 = fma(u, u, t.var), h = Real(0.5) * u;
-    w[0] = fma(Real(0.5), m2, -h) - p;
-    w[1] = fma(Real(3), p, Real(1) - m2);
-    w[2] = fma(Real(-3), p, fma(Real(0.5), m2, h));
-    w[3] = p;
   } else {
-    const Real d2 = d * d;
-    const Real p = d2 * (d2 * t.beta);
-    const Real m2 = fma(u, u, t.var), m3 = u * fma(Real(2), t.var, m2);
-    const Real q3 = (m3 - u) * Real(1.0 / 6.0);
-    const Real q2 = fma(Real(0.5), m2 - m3, u);
-    const Real q0 = fma(Real(0.5), m2 - u, -q3);
-    w[0] = q0 + p;
-    w[1] = fma(Real(-4), p, Real(1) - q0 - q2 - q3);
-    w[2] = fma(Real(6), p, q2);
-    w[3] = fma(Real(-4), p, q3);
-    w[4] = p;
+    const Real m = fabs(v);
+    const Real d = fmax(t.a - m, Real(0));
+    if constexpr (L == 2) {
+      const Real p = d * (d * t.beta);
+      w[0] = p + fmax(-v, Real(0));
+      w[1] = fma(Real(-2), p, Real(1) - m);
+      w[2] = p + fmax(v, Real(0));
+    } else {
+      // h: half the outer weights' sum, x: half their difference, signed
+      const Real p = (d * d) * (d * t.beta);
+      const Real h = fma(Real(0.25) * v, v, t.c);
+      const Real x = copysign(h - p, v);
+      const Real s = Real(0.5) - h, y = fma(Real(-3), x, v);
+      w[0] = h - x;
+      w[1] = s - y;
+      w[2] = s + y;
+      w[3] = h + x;
+    }
   }
 }
 
@@ -214,7 +221,7 @@ constexpr Tab<Real> make_wtab(int l, int kind) {
 // Returns false (and a message) on invalid input or an internal inconsistency.
 bool build_table(int l, int kind, double a, Tab<double>& out, const char** err);
 
-// Host: the constants of tfac_eval from a kind-2 table of 0 < a <= 1/2.
+// Host: the constants of tfac_split and tfac_eval from a kind-2 table of 0 < a <= 1/2.
 TFac<double> make_tfac(int l, double a, const Tab<double>& t);
 
 template <class Real>

@@ -1,0 +1,38 @@
+"""T_l's weights from its moments are as exact as those from its polynomial
+table, in both precisions and over the Courant numbers of c dt <= dx / 2: the
+functions that the particle kernel calls, compiled for the host with the fused
+multiply-adds that the device makes of them, against the factor in long double.
+
+In units of the rounding of a number just below one (2^-24 or 2^-53), a sum
+rounded once is off by up to a half, so the root mean square over a place's
+weights may be the table's or a half, whichever is larger, and the largest
+error the table's or that of three such roundings."""
+import ctypes
+import os
+import subprocess
+
+import pytest
+
+from paper_1909_09613_amd import build as B
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("weights") / "libweights.so")
+    subprocess.run([B.HIPCC, "-x", "hip", "--offload-host-only", "-O2", "-std=c++17", "-mfma", "-ffp-contract=fast",
+                    "-fPIC", "-shared", "-I", B.CSRC, os.path.join(HERE, "weights_host.cpp"),
+                    os.path.join(B.CSRC, "tables.cpp"), "-o", out], check=True)
+    return ctypes.CDLL(out)
+
+
+@pytest.mark.parametrize("fp32", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("order", [1, 2, 3])
+def test_moments_as_exact_as_the_table(host, order, fp32):
+    for a in (0.1, 0.137, 0.212, 0.25, 0.3, 0.35, 0.37, 0.4, 0.45, 0.49, 0.4999, 0.5):
+        e = (ctypes.c_double * 4)()
+        host.weight_errors(order, fp32, ctypes.c_double(a), 20000, e)
+        table, moments, table_max, moments_max = e
+        assert 0.0 <= moments <= max(table, 0.5), (a, list(e))
+        assert 0.0 <= moments_max <= max(table_max, 1.5), (a, list(e))
