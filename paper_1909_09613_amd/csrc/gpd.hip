@@ -98,66 +98,8 @@ __device__ __forceinline__ Real gather3(const Real* Fc, int px, int pz, const Re
   return s;
 }
 
-// Weights of a B-spline table's NW nodes at g, up to the cubic one in the
-// closed form of its polynomials (checked where the tables are built).  The
-// cubic in its symmetric form, 11 instructions against 12 for the four Horner
-// polynomials: with t = 1 - g, w0 = t^3/6, w1 = 2/3 - g^2 + g^3/2, w2 the same
-// at t, w3 = g^3/6.  The closed forms need at most two constants that are no
-// immediate operands, where FP64 read both tables from scalar memory for
-// every particle.
-template <int L, int NW, class Real>
-__device__ __forceinline__ void wtab_eval(const Tab<Real>& T, Real g, Real* w) {
-  if constexpr (L == 3 && NW == 4) {
-    const Real t = Real(1) - g;
-    const Real g2 = g * g, t2 = t * t;
-    w[0] = t2 * (t * Real(1.0 / 6.0));
-    w[1] = fma(g2, fma(g, Real(0.5), Real(-1)), Real(2.0 / 3.0));
-    w[2] = fma(t2, fma(t, Real(0.5), Real(-1)), Real(2.0 / 3.0));
-    w[3] = g2 * (g * Real(1.0 / 6.0));
-  } else if constexpr (L == 2 && NW == 3) {
-    const Real t = Real(1) - g;
-    w[0] = t * (t * Real(0.5));
-    w[1] = fma(g, t, Real(0.5));
-    w[2] = g * (g * Real(0.5));
-  } else if constexpr (L == 1 && NW == 2) {
-    w[0] = Real(1) - g;
-    w[1] = g;
-  } else {
-    tab_eval<L, NW, false>(T, g, w);
-  }
-}
-
-// Weight differences w_k(e) - w_k(g) = d * (divided difference), d = e - g,
-// for a table's L + 1 nodes.  For the cubic B-spline with h2 = g + e and
-// h3 = g^2 + g e + e^2: the differences of the four closed forms above are
-// d (h3/6), d ((h2 - 1)/2 - h3/6) and d (h3/2 - h2) for nodes 3, 0 and 1, and
-// node 2 takes minus their sum (the weights sum to one), 12 instructions
-// against 16; the quadratic one's d h2/2, d (h2/2 - 1) and minus their sum.
-template <int L, bool CONSTTAB, class Real>
-__device__ __forceinline__ void wtab_diff(const Tab<Real>& T, Real g, Real e, Real d, Real* dw) {
-  if constexpr (L == 3) {
-    const Real h2 = g + e;
-    const Real h3 = fma(h2, e, g * g);
-    const Real q = h3 * (d * Real(1.0 / 6.0));
-    dw[3] = q;
-    dw[0] = fma(h2 - Real(1), d * Real(0.5), -q);
-    dw[1] = fma(Real(3), q, -(d * h2));
-    dw[2] = -(dw[0] + dw[1]) - q;
-  } else if constexpr (L == 2) {
-    const Real q = (g + e) * (d * Real(0.5));
-    dw[0] = q - d;
-    dw[1] = fma(Real(-2), q, d);
-    dw[2] = q;
-  } else if constexpr (L == 1) {
-    dw[0] = -d;
-    dw[1] = d;
-  } else {
-    tab_diff<L, CONSTTAB>(T, g, e, d, dw);
-  }
-}
-
 // Whether a table of order l <= 3 holds the B-spline polynomials in the node
-// order of wtab_eval's closed forms.
+// order of wtab_eval's closed forms (tables.hpp).
 template <class Real>
 constexpr bool is_bspline(const Tab<Real>& t, int l) {
   constexpr double ref[3][4][4] = {

@@ -1,7 +1,8 @@
-"""T_l's weights from its moments are as exact as those from its polynomial
-table, in both precisions and over the Courant numbers of c dt <= dx / 2: the
-functions that the particle kernel calls, compiled for the host with the fused
-multiply-adds that the device makes of them, against the factor in long double.
+"""T_l's weights from its moments and the B-spline's weight differences in closed
+form are as exact as those from the polynomial tables, in both precisions and
+over the Courant numbers of c dt <= dx / 2: the functions that the particle
+kernel calls, compiled for the host with the fused multiply-adds that the device
+makes of them, against the factor and the spline in long double.
 
 In units of the rounding of a number just below one (2^-24 or 2^-53), a sum
 rounded once is off by up to a half, so the root mean square over a place's
@@ -36,3 +37,14 @@ def test_moments_as_exact_as_the_table(host, order, fp32):
         table, moments, table_max, moments_max = e
         assert 0.0 <= moments <= max(table, 0.5), (a, list(e))
         assert 0.0 <= moments_max <= max(table_max, 1.5), (a, list(e))
+
+
+# (the cubic one in FP32 takes a node's difference from the others': the weights
+# of a step then sum to zero, and the errors of three roundings add up in it)
+@pytest.mark.parametrize("order,fp32", [(1, 0), (1, 1), (2, 0), (2, 1), (3, 0)])
+def test_differences_as_exact_as_the_table(host, order, fp32):
+    e = (ctypes.c_double * 4)()
+    host.difference_errors(order, fp32, 100000, e)
+    table, closed, table_max, closed_max = e
+    # 2%: the largest of 1e5 places varies by about that much
+    assert 0.0 <= closed <= table and closed_max <= 1.02 * table_max, list(e)

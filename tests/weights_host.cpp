@@ -1,5 +1,6 @@
-// Host side of test_weights_error.py: errors of T_l's weights, as the particle
-// kernel evaluates them, against the factor itself in long double.
+// Host side of test_weights_error.py: errors of T_l's weights and of the
+// B-spline's weight differences, as the particle kernel evaluates them, against
+// the functions themselves in long double.
 #include <math.h>
 
 #include <algorithm>
@@ -62,6 +63,54 @@ void compare(double a, int n, double out[4]) {
   }
 }
 
+// W_l(y), likewise.
+long double bspline(int l, long double y) {
+  long double s = 0.0L, b = 1.0L, fact = 1.0L;
+  for (int i = 2; i <= l; ++i) fact *= i;
+  for (int j = 0; j <= l + 1; ++j) {
+    const long double p = y + 0.5L * (l + 1) - j;
+    if (p > 0.0L) s += b * powl(p, l);
+    b = -b * (l + 1 - j) / (j + 1);
+  }
+  return s / fact;
+}
+
+template <class Real, int L>
+void compare_differences(int n, double out[4]) {
+  constexpr Tab<Real> t = make_wtab<Real>(L, 1);
+  const long double unit = sizeof(Real) == 4 ? 0x1p-24L : 0x1p-53L;
+  std::mt19937_64 rng(19);
+  double sum[2] = {0, 0}, most[2] = {0, 0};
+  for (int i = 0; i < n; ++i) {
+    const Real g = std::min(Real((rng() >> 11) * 0x1p-53), Real(1) - Real(unit));
+    // a step of up to 1/16 cell (longer ones take S1 - S0) that ends in the cell
+    const Real e = std::min(std::max(g + Real(((rng() >> 11) * 0x1p-53 - 0.5) / 8), Real(0)), Real(1));
+    const Real d = e - g;
+    if (d == Real(0) || (long double)d != (long double)e - (long double)g) continue;
+    Real dw[2][L + 1];
+    tab_diff<L, true>(t, g, e, d, dw[0]);
+    wtab_diff<L, true>(t, g, e, d, dw[1]);
+    for (int j = 0; j <= L; ++j) {
+      // the particle's distance from node j
+      const long double o = (long double)t.sigma - (t.first + j);
+      // the mean of dW_l/dy = W_{l-1}(y + 1/2) - W_{l-1}(y - 1/2), at most a
+      // parabola here, by Simpson's rule
+      auto slope = [&](long double y) { return bspline(L - 1, o + y + 0.5L) - bspline(L - 1, o + y - 0.5L); };
+      const long double m = 0.5L * ((long double)g + e);
+      const long double x = L == 1 ? slope(m) : (slope(g) + 4.0L * slope(m) + slope(e)) / 6.0L;
+      for (int k = 0; k < 2; ++k) {
+        const double r = (double)((dw[k][j] / (long double)d - x) / unit);
+        sum[k] += r * r;
+        most[k] = std::max(most[k], fabs(r));
+      }
+    }
+  }
+  for (int k = 0; k < 2; ++k) {
+    out[k] = sqrt(sum[k] / n);
+    out[2 + k] = most[k];
+  }
+}
+
 }  // namespace
 
 // out: root mean square error of a place's weights (table, moments), largest
@@ -71,4 +120,12 @@ extern "C" void weight_errors(int l, int fp32, double a, int n, double out[4]) {
   if (l == 1) fp32 ? compare<float, 1>(a, n, out) : compare<double, 1>(a, n, out);
   if (l == 2) fp32 ? compare<float, 2>(a, n, out) : compare<double, 2>(a, n, out);
   if (l == 3) fp32 ? compare<float, 3>(a, n, out) : compare<double, 3>(a, n, out);
+}
+
+// The same of the weight differences over the step (table, closed form).
+extern "C" void difference_errors(int l, int fp32, int n, double out[4]) {
+  for (int k = 0; k < 4; ++k) out[k] = -1.0;
+  if (l == 1) fp32 ? compare_differences<float, 1>(n, out) : compare_differences<double, 1>(n, out);
+  if (l == 2) fp32 ? compare_differences<float, 2>(n, out) : compare_differences<double, 2>(n, out);
+  if (l == 3) fp32 ? compare_differences<float, 3>(n, out) : compare_differences<double, 3>(n, out);
 }
