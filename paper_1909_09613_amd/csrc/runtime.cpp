@@ -288,12 +288,9 @@ hipError_t host_copy(pic_ctx* c, void* dst, const void* src, size_t bytes, hipMe
 // The smallest pitch >= w that is r modulo m.
 int pitch_from(int w, int r, int m) { return w + ((r - w) % m + m) % m; }
 
-// Row and plane pitch of a staged window of w[0] x w[1] (x w[2]) nodes.
-//
-// In mixed precision the fixed pitches of FixedPitch (fixed[2]: row, plane)
-// when the window fits them, so that the kernel's fixed-pitch variant runs
-// (2D: tiles of 16 cells along x1 and more).  Else, padded, the pitch that
-// puts the rows that the LDS serves together side by side on its banks: the
+// Row and plane pitch of a staged window of w[0] x w[1] (x w[2]) nodes: its own
+// rows (3D mixed precision: planes of a multiple of 8 nodes), or, padded, the pitch
+// that puts the rows that the LDS serves together side by side on its banks: the
 // particles of a wave lie in the cells of the sort's order (x1 first; in 3D
 // mixed precision every second row before the others), and the LDS serves
 // 32 4-byte or 16 8-byte lanes at once, so a tile narrower than that has 2 or
@@ -303,13 +300,8 @@ int pitch_from(int w, int r, int m) { return w + ((r - w) % m + m) % m; }
 // cubic FP64 (16x16, current rows 26 -> 40) 295 -> 289 us, 256x128 cubic mixed
 // (8x8, rows of the fixed pitches -> 24) 32.3 -> 29.5 us; 3D mixed precision as in
 // FixedPitch.
-void window_pitches(int ndim, bool f64, const int tile[3], const int w[3], const int fixed[2], bool pad, int p[2]) {
+void window_pitches(int ndim, bool f64, const int tile[3], const int w[3], bool pad, int p[2]) {
   p[0] = w[0];
-  if (!f64 && w[0] <= fixed[0] && (ndim == 2 ? tile[0] >= 16 : fixed[0] * w[1] <= fixed[1])) {
-    p[0] = fixed[0];
-    p[1] = (ndim == 2) ? p[0] * w[1] : fixed[1];
-    return;
-  }
   if (pad) {
     if (f64 || ndim == 2)
       p[0] = tile[0] >= 8 ? pitch_from(w[0], 8, 16) : pitch_from(w[0], 4, 8);
@@ -318,6 +310,16 @@ void window_pitches(int ndim, bool f64, const int tile[3], const int w[3], const
   }
   p[1] = p[0] * w[1];
   if (ndim == 3 && !f64) p[1] = (pad && tile[0] < 16) ? pitch_from(p[1], 16, 32) : (p[1] + 7) / 8 * 8;
+}
+
+// Mixed precision: the pitches (row; in 3D row and plane) that the particle kernel
+// has a variant compiled for, if the window fits them.
+template <int DIM>
+bool fixed_pitches(const int fixed[2], const int w[3], int p[2]) {
+  if (w[0] > fixed[0] || (DIM == 3 && fixed[0] * w[1] > fixed[1])) return false;
+  p[0] = fixed[0];
+  p[1] = DIM == 3 ? fixed[1] : fixed[0] * w[1];
+  return true;
 }
 
 // Reach of a table's nodes relative to the particle's cell: base - cell is 0
@@ -467,22 +469,46 @@ pic_status apply_tiling(pic_ctx* c) {
     c->jw[k] = c->guard[k] + 2 * (c->sort_every - 1) + span_d[k] + 1;
     if (c->guard[k] < c->tile[k]) return c->fail(PIC_ERR_ARG, "margin must exceed sort_every");
   }
-  const int* ffix = nd == 2 ? FixedPitch<2>::f : FixedPitch<3>::f;
-  const int* jfix = nd == 2 ? FixedPitch<2>::j : FixedPitch<3>::j;
   // FP32: fine and coarse fixed-point current windows and a cell count in
   // 2D (7 ints per node), the fine windows in 3D (3 ints; its coarse ones
-  // are in global memory); FP64: FP64 current windows.  Padded rows where
-  // two groups still share a CU: both windows', the current's alone (its
-  // atomics lose more to conflicts than the reads), or none.
+  // are in global memory); FP64: FP64 current windows.
   const size_t rs = sizeof(Real);
   size_t jcap = 0;
-  for (int pad = 2; pad >= 0; --pad) {
-    window_pitches(nd, c->f64(), c->tile, c->fw, ffix, pad == 2, c->fp);
-    window_pitches(nd, c->f64(), c->tile, c->jw, jfix, pad >= 1, c->jp);
+  auto lds_of = [&] {
     const size_t fcap = (size_t)(nd == 3 ? c->fp[1] * c->fw[2] : c->fp[0] * c->fw[1]);
     jcap = (size_t)(nd == 3 ? c->jp[1] * c->jw[2] : c->jp[0] * c->jw[1]);
-    c->lds = 6 * rs * fcap + (c->f64() ? 3 * sizeof(double) : (nd == 2 ? 7 : 3) * sizeof(int)) * jcap;
-    if (c->lds <= std::min<size_t>(c->lds_budget, kDefaultLds)) break;
+    return 6 * rs * fcap + (c->f64() ? 3 * sizeof(double) : (nd == 2 ? 7 : 3) * sizeof(int)) * jcap;
+  };
+  // Padded rows where two groups still share a CU: both windows', the current's
+  // alone (its atomics lose more to conflicts than the reads), or none.
+  auto padded = [&] {
+    for (int pad = 2; pad >= 0; --pad) {
+      window_pitches(nd, c->f64(), c->tile, c->fw, pad == 2, c->fp);
+      window_pitches(nd, c->f64(), c->tile, c->jw, pad >= 1, c->jp);
+      // 2D mixed precision: each window of a tile of 16 cells along x1 and more
+      // that fits its fixed pitch takes it
+      if (nd == 2 && !c->f64() && c->tile[0] >= 16) {
+        (void)fixed_pitches<2>(FixedPitch<2>::f, c->fw, c->fp);
+        (void)fixed_pitches<2>(FixedPitch<2>::j, c->jw, c->jp);
+      }
+      if (lds_of() <= std::min<size_t>(c->lds_budget, kDefaultLds)) break;
+    }
+    return lds_of();
+  };
+  // 3D mixed precision: the fixed pitches where the particle kernel has its
+  // variant for them (l <= 2, both windows fit) and they keep two groups on a CU,
+  // or, where no rows do, at all fit.
+  auto fixed3 = [&] {
+    return nd == 3 && !c->f64() && c->order <= 2 &&
+           fixed_pitches<3>(FixedPitch<3>::f, c->fw, c->fp) && fixed_pitches<3>(FixedPitch<3>::j, c->jw, c->jp);
+  };
+  const bool fixed = fixed3();
+  const size_t fixed_lds = fixed ? lds_of() : 0;
+  if (fixed && fixed_lds <= std::min<size_t>(c->lds_budget, kDefaultLds)) {
+    c->lds = fixed_lds;
+  } else {
+    c->lds = padded();
+    if (fixed && c->lds > (size_t)kDefaultLds && fixed_lds <= (size_t)c->lds_budget && fixed3()) c->lds = lds_of();
   }
   if (nd == 3 && !c->f64() && 3 * jcap > (size_t)kCoarseCap)
     return c->fail(PIC_ERR_ARG, "tile too large for the coarse current windows");

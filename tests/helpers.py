@@ -113,6 +113,41 @@ def current_tol(spec, k, fp32):
     return max(2e-4, 2.0 ** -25 / step)
 
 
+def check_one_step(orc, spec, precision, amp=0.05, seed=21, tiling=None):
+    """One particle step (pic_gather_push_deposit) of one run from a seeded
+    random state against the oracle's, to the one-step bounds; tiling, if given,
+    the arguments of pic_set_tiling."""
+    import paper_1909_09613_amd as wt
+    fp32 = precision == wt.PIC_MIXED32
+    sp, E, B = random_state(spec, seed, amp, fp32=fp32)
+    g = oracle_grid(orc, spec)
+    g.E[:] = E
+    g.B[:] = B
+    g.zero_J()
+    ref = copy_species(sp)
+    for s in ref:
+        g.push_species(s["x"], s["u"], s["qm"], s["Q"])
+    sim = wt.Sim([spec], precision)
+    try:
+        if tiling is not None:
+            wt.pic_set_tiling(sim.ctx, *tiling)
+        sim.set_species(0, sp)
+        sim.set_fields(0, E, B)
+        sim.gpd()
+        got = [sim.particles(0, s) for s in range(2)]
+        J = sim.fields(0)[2]
+        d = sim.diagnostics(0)
+    finally:
+        sim.close()
+    assert d.n_nonfinite == 0 and d.n_out_of_range == 0
+    ex, eu = particle_errors(spec, ref, got)
+    tol = 2e-6 if fp32 else 1e-12
+    assert ex <= tol and eu <= tol, (ex, eu)
+    scale = abs_current_scale(orc, spec, sp, E, B)
+    for k in range(3):
+        assert np.max(np.abs(J[k] - g.J[k])) / scale[k] <= current_tol(spec, k, fp32), k
+
+
 def trajectory_vs_oracle(orc, spec, amp, steps, precision, seed=11):
     """`steps` graph-replayed steps (pic_step) of one run from a seeded
     random state with fields of amplitude `amp`, and the same steps of the
