@@ -3,6 +3,8 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "../../include/wtpic.h"
 #include "common.hpp"
 
@@ -30,6 +32,7 @@ struct SortArgs {
   int tile[3];
   int tc;             // cells of a full tile
   int kcap;           // ranks within a cell ordered level by level (arrange pass)
+  int dense;          // most particles lie in segments larger than kArrangeCap
   int* counts;        // nkeys: particles per segment (zero between sorts)
   int* seg;           // nkeys + 1
   int* keys;          // np_total
@@ -53,14 +56,15 @@ constexpr int kArrangeBlock = 1024;
 constexpr int kArrangeItems = 8;
 constexpr int kArrangeCap = kArrangeItems * kArrangeBlock;
 constexpr int kArrangeOrderCells = 2048, kArrangeOrderCount = 64;
-inline size_t arrange_lds(int tc, int kcap) {
-  const size_t keys = tc <= kArrangeOrderCells ? (size_t)2 * (tc + kArrangeCap) : 0;
+inline size_t arrange_lds(int tc, int kcap, bool dense) {
+  const size_t keys = !dense && tc <= kArrangeOrderCells ? (size_t)2 * (tc + kArrangeCap) : 0;
   return (size_t)4 * (2 * tc + kcap + 2) + (size_t)2 * kcap * tc + keys + 16;
 }
-// Levels the arrange pass orders one by one for a tile of tc cells.
-inline int arrange_kcap(int tc) {
-  const int k = 8192 / (tc > 0 ? tc : 1);
-  return k < 1 ? 1 : (k > 64 ? 64 : k);
+// Levels the arrange pass orders one by one for a tile of tc cells; dense: in the
+// keys' place too (up to 192 more: one thread adds the levels up).
+inline int arrange_kcap(int tc, bool dense) {
+  const int k = 8192 / (tc > 0 ? tc : 1), more = dense && tc <= kArrangeOrderCells ? std::min(kArrangeCap / tc, 192) : 0;
+  return (k < 1 ? 1 : (k > 64 ? 64 : k)) + more;
 }
 
 template <class Real>

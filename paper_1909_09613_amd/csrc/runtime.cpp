@@ -425,6 +425,16 @@ pic_status upload_runs(pic_ctx* c) {
   return c->hip(e, "run table upload");
 }
 
+// Whether most particles belong to runs whose full tiles hold more particles of a
+// species than the sort orders by place within their cells.
+bool dense_segments(const pic_ctx* c) {
+  const long long cells = (long long)c->tile[0] * c->tile[1] * c->tile[2];
+  long long dense = 0;
+  for (const RunHost& H : c->runs)
+    if (H.d.ppc_per_species * cells > kArrangeCap) dense += 2 * H.nps;
+  return 2 * dense > c->np_total;
+}
+
 // Tiling-dependent state: tiles per run, windows, guard, LDS size, and the
 // device tables that depend on them.
 template <class Real>
@@ -611,7 +621,8 @@ SortArgs<Real> sort_args(pic_ctx* c) {
   a.nkeys = 2 * c->G;
   for (int k = 0; k < 3; ++k) a.tile[k] = c->tile[k];
   a.tc = c->tile[0] * c->tile[1] * c->tile[2];
-  a.kcap = arrange_kcap(a.tc);
+  a.dense = dense_segments(c) ? 1 : 0;
+  a.kcap = arrange_kcap(a.tc, a.dense != 0);
   a.counts = reinterpret_cast<int*>(c->S + c->lay.s_counts);
   a.seg = reinterpret_cast<int*>(c->S + c->lay.s_seg);
   a.keys = reinterpret_cast<int*>(c->S + c->lay.s_keys);

@@ -319,7 +319,18 @@ __device__ __forceinline__ unsigned order_key(typename P::Real fx, typename P::R
 // fits without scratch, whose allocation a stream's first launch pays with some
 // 200 us (in groups of 512 the items' 32 registers do not fit).
 // 19M particles in mixed precision 638 -> 477 us, 0.87M in FP64 48 -> 44 us.
-template <class P, int DIM>
+//
+// DENSE: most particles lie in segments of more than kArrangeCap.  All segments
+// take the arrival order, and the keys' place holds as many levels more, since
+// ranks beyond the levels lie cell by cell, whole waves in one cell, whose atomics
+// all meet at one address (a longer chain than the levels' random starts).
+// Particle kernel, without -> with the levels in the keys' place (0.45 dx, particles
+// per cell and species): 512x512 cubic FP64 at 40 1153 -> 820 us, quadratic 750 ->
+// 628, cubic at 70 3860 -> 1573; 40^3 linear FP64 at 150 1198 -> 488; 1024x512 cubic
+// mixed at 40 2660 -> 1023; 64^3 quadratic mixed at 70 2500 -> 1266.  (The even
+// cells of a row before the odd ones, which pays in arrival order while ranks lie
+// beyond the levels, 1153 -> 1085, does not with them, 628 -> 737.)
+template <class P, int DIM, bool DENSE>
 __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
   if (!A.st->sort_request) return;
@@ -354,10 +365,10 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
     const int org[3] = {__builtin_amdgcn_readfirstlane(where.x), __builtin_amdgcn_readfirstlane(where.y),
                         __builtin_amdgcn_readfirstlane(where.z)};
     // a segment of up to kArrangeCap particles keeps each particle's cell and
-    // rank in registers and orders the cells; a larger one (dense cells, or
-    // more particles per cell than any workload here has) takes the arrival
-    // order, its ranks through global memory
-    const bool ordered = TC <= kArrangeOrderCells && n <= kArrangeCap;
+    // rank in registers and orders the cells; a larger one (dense cells, many
+    // particles per cell) takes the arrival order, its ranks through global
+    // memory
+    const bool ordered = !DENSE && TC <= kArrangeOrderCells && n <= kArrangeCap;
     for (int i = tid; i < TC; i += kArrangeBlock) cnt[i] = 0;
     if (tid == 0) cmax_s = 0;
     __syncthreads();
@@ -573,10 +584,14 @@ hipError_t launch_sort(const SortArgs<typename P::Real>& a, int ndim, hipStream_
   else
     hipLaunchKernelGGL((sort_scatter<P, 3>), dim3(grid), dim3(kSortBlock), 0, s, a);
   const int agrid = a.nkeys < 1024 ? a.nkeys : 1024;
-  if (ndim == 2)
-    hipLaunchKernelGGL((sort_arrange<P, 2>), dim3(agrid), dim3(kArrangeBlock), arrange_lds(a.tc, a.kcap), s, a);
-  else
-    hipLaunchKernelGGL((sort_arrange<P, 3>), dim3(agrid), dim3(kArrangeBlock), arrange_lds(a.tc, a.kcap), s, a);
+  const size_t lds = arrange_lds(a.tc, a.kcap, a.dense);
+  if (ndim == 2) {
+    if (a.dense) hipLaunchKernelGGL((sort_arrange<P, 2, true>), dim3(agrid), dim3(kArrangeBlock), lds, s, a);
+    else hipLaunchKernelGGL((sort_arrange<P, 2, false>), dim3(agrid), dim3(kArrangeBlock), lds, s, a);
+  } else {
+    if (a.dense) hipLaunchKernelGGL((sort_arrange<P, 3, true>), dim3(agrid), dim3(kArrangeBlock), lds, s, a);
+    else hipLaunchKernelGGL((sort_arrange<P, 3, false>), dim3(agrid), dim3(kArrangeBlock), lds, s, a);
+  }
   return hipGetLastError();
 }
 

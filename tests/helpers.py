@@ -113,13 +113,18 @@ def current_tol(spec, k, fp32):
     return max(2e-4, 2.0 ** -25 / step)
 
 
-def check_one_step(orc, spec, precision, amp=0.05, seed=21, tiling=None):
+def check_one_step(orc, spec, precision, amp=0.05, seed=21, tiling=None, place=None):
     """One particle step (pic_gather_push_deposit) of one run from a seeded
     random state against the oracle's, to the one-step bounds; tiling, if given,
-    the arguments of pic_set_tiling."""
+    the arguments of pic_set_tiling, place(x) a change of each species' positions."""
     import paper_1909_09613_amd as wt
     fp32 = precision == wt.PIC_MIXED32
     sp, E, B = random_state(spec, seed, amp, fp32=fp32)
+    if place is not None:
+        for s in sp:
+            place(s["x"])
+            if fp32:
+                s["x"], s["u"] = inputs.quantize_fp32(s["x"], s["u"])
     g = oracle_grid(orc, spec)
     g.E[:] = E
     g.B[:] = B
