@@ -473,6 +473,29 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
       mb[1] = fmaxf(mb[1], (float)R.a[1] * fabsf(u1) * ig);
       mb[2] = fmaxf(mb[2], (DIM == 2 ? 1.0f : (float)R.a[2]) * fabsf(u2) * ig);
     };
+    // slots o0, o0 + kArrangeBlock, .. from their sources, array by array
+    auto fill = [&](int o0, const int* src) {
+      auto move = [&](const auto* from, auto* to, auto* v) {
+#pragma unroll
+        for (int u = 0; u < W; ++u) v[u] = from[src[u]];
+#pragma unroll
+        for (int u = 0; u < W; ++u)
+          if (o0 + u * kArrangeBlock < n) to[s0 + o0 + u * kArrangeBlock] = v[u];
+      };
+      int iv[W];
+      Real rv[W], uv[3][W];
+      if (!P::kAbs) move(S.cell, D.cell, iv);
+      move(S.tag, D.tag, iv);
+#pragma unroll
+      for (int d = 0; d < DIM; ++d) move(S.pos[d], D.pos[d], rv);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) move(S.u[d], D.u[d], uv[d]);
+      if (!P::kAbs) {
+#pragma unroll
+        for (int u = 0; u < W; ++u)
+          if (o0 + u * kArrangeBlock < n) bound((float)uv[0][u], (float)uv[1][u], (float)uv[2][u]);
+      }
+    };
     if (ordered) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -505,26 +528,23 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
         const int o0 = tid + u0 * kArrangeBlock;
 #pragma unroll
         for (int u = 0; u < W; ++u) src[u] = s0 + keys[min(o0 + u * kArrangeBlock, n - 1)];
-        auto move = [&](const auto* from, auto* to, auto* v) {
+        fill(o0, src);
+      }
+    } else if (DENSE) {
+      // the sources through the tags' place of the current store, which holds
+      // nothing yet: 4 bytes of a particle are scattered there, not all of it
+      // (21M particles in mixed precision 2.76 -> 1.57 ms, 21M in FP64 1.40 -> 1.10)
+      for (int i = tid; i < n; i += kArrangeBlock)
+        D.tag[s0 + slot_of(cell_in_tile<P, DIM>(S, s0 + i, org, A.tile), A.keys[s0 + i])] = i;
+      __syncthreads();
+      for (int o0 = tid; o0 < n; o0 += W * kArrangeBlock) {
+        int src[W];
 #pragma unroll
-          for (int u = 0; u < W; ++u) v[u] = from[src[u]];
-#pragma unroll
-          for (int u = 0; u < W; ++u)
-            if (o0 + u * kArrangeBlock < n) to[s0 + o0 + u * kArrangeBlock] = v[u];
-        };
-        int iv[W];
-        Real rv[W], uv[3][W];
-        if (!P::kAbs) move(S.cell, D.cell, iv);
-        move(S.tag, D.tag, iv);
-#pragma unroll
-        for (int d = 0; d < DIM; ++d) move(S.pos[d], D.pos[d], rv);
-#pragma unroll
-        for (int d = 0; d < 3; ++d) move(S.u[d], D.u[d], uv[d]);
-        if (!P::kAbs) {
-#pragma unroll
-          for (int u = 0; u < W; ++u)
-            if (o0 + u * kArrangeBlock < n) bound((float)uv[0][u], (float)uv[1][u], (float)uv[2][u]);
+        for (int u = 0; u < W; ++u) {
+          const int o = o0 + u * kArrangeBlock;
+          src[u] = s0 + (o < n ? D.tag[s0 + o] : 0);
         }
+        fill(o0, src);
       }
     } else {
       for (int i = tid; i < n; i += kArrangeBlock) {
