@@ -610,13 +610,11 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
   const Real twelfth = Real(1) / Real(12);
   const Real half = Real(0.5);
   // per-axis constants of the loop.  A particle's place along an axis is
-  // q = wrap(c - co, n), counted from lo (tile-relative), the lowest place
-  // whose stencils the staged windows hold; they hold those up to qmax.
-  // Counted from there the test is one compare, and the windows' offsets
-  // (half-lattice, T and union stencils, cell counts) take lo in.  Where the
-  // windows are wider than the axis, every cell has a place in them, and the
-  // box is centred in the axis's n places as far as the windows reach.
-  // In an inner tile, whose places all lie inside the grid with a cell to
+  // q = wrap(c - co, n), counted from the box's low end, the lowest place whose
+  // stencils the staged windows hold; they hold those up to qmax, the box's high
+  // end (a box as wide as the axis and more: every cell once).  Counted from
+  // there the test is one compare, and the windows' offsets (half-lattice, T and
+  // union stencils, cell counts) hold for every tile.  In an inner tile, whose places all lie inside the grid with a cell to
   // spare below and two above (a position can round up onto a cell face),
   // c - co needs no wrap and a moved particle's cell no periodic image, some
   // twenty vector instructions of 600 per particle.  With the waves' stencil
@@ -627,25 +625,20 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
   // out; the FP64 path and the 512-thread 3D kernel need their vector
   // registers for their own state, within 128 for four waves per SIMD)
   auto pin = [](int x) { return (P::kAbs || (DIM == 3 && GpdShape<L, DIM, SKIP>::kWide)) ? x : in_vgpr(x); };
-  int co[3], lo_[3], nn[3], qmax[3], hoff[3], toff[3], uoff[3], joff[3];
+  int co[3], nn[3], qmax[3], hoff[3], toff[3], uoff[3], joff[3];
   bool inside = true;
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    const int n = R.n[d];
-    const int slack = max(0, n - 1 - (bb[2 * d + 1] - bb[2 * d]));
-    const int rlo = max(fo[d] - R.glo[d], jo[d] - R.dlo[d]);
-    const int rhi = min(fo[d] + fs[d] - 1 - R.ghi[d], jo[d] + jsz[d] - 1 - R.dhi[d]);
-    const int lo = (rhi - rlo < n) ? rlo : min(max(bb[2 * d] - (slack >> 1), rlo), rhi - n + 1);
-    const int c0 = wrap_sub(org[d] + lo, n);
-    lo_[d] = lo;
-    if (d < DIM) inside = inside && c0 >= 1 && c0 + (rhi - lo) <= n - 3;
+    const int n = R.n[d], len = bb[2 * d + 1] - bb[2 * d];
+    const int c0 = wrap_sub(org[d] + bb[2 * d], n);
+    if (d < DIM) inside = inside && c0 >= 1 && c0 + len <= n - 3;
     co[d] = pin(c0);
     nn[d] = pin(n);
-    qmax[d] = pin(min(rhi - lo, n - 1));
-    hoff[d] = pin(kWh.first - fo[d] + lo);
-    toff[d] = pin((kMoments ? R.tf[d].first : R.T[d].first) - fo[d] + lo);
-    uoff[d] = pin(kWi.first - jo[d] + lo);
-    joff[d] = pin(lo - jo[d]);
+    qmax[d] = pin(min(len, n - 1));
+    hoff[d] = pin(kWh.first - R.glo[d]);
+    toff[d] = pin((kMoments ? R.tf[d].first : R.T[d].first) - R.glo[d]);
+    uoff[d] = pin(kWi.first - R.dlo[d]);
+    joff[d] = pin(-R.dlo[d]);
   }
   // (one scalar, so that the loop branches on it with a scalar compare)
   int inner = __builtin_amdgcn_readfirstlane(inside ? 1 : 0);
@@ -1282,8 +1275,8 @@ __device__ __forceinline__ void gpd_tile(const GpdArgs<typename P::Real>& A, con
           lo = 0;
           hi = min(A.tile[d], R.n[d] - org[d]) - 1;
         } else {
-          lo += lo_[d];
-          hi += lo_[d];
+          lo += bb[2 * d];
+          hi += bb[2 * d];
         }
         need = need || (hi - lo > A.guard[d]);
         // a box that drifted a whole period keeps canonical coordinates
