@@ -96,7 +96,9 @@ typedef struct {
 
 /* Caller-owned device buffers, sized by pic_query_layout. */
 typedef struct {
-  void *particles;   /* two particle stores (the sort ping-pongs between them) */
+  void *particles;   /* two particle stores: the first holds the particles between calls,
+                        the sort and pic_set_particles / pic_get_particles pass them
+                        through the second */
   void *fields;      /* E and B of every run */
   void *current;     /* FP64 J of every run */
   void *scratch;     /* run tables, tile segments, sort keys, diagnostics */

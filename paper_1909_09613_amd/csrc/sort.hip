@@ -10,10 +10,10 @@
 // arrange  one block per segment: order the segment back into the current
 //          store by (rank within its cell, cell): first every cell's first
 //          particle, cells in tile order, then every cell's second particle,
-//          and so on, ranked by their place in the cell.  The lanes of a wave then hold particles of 64
-//          nearby cells, one each, so that the gather reads and the current
-//          atomics of a wave touch distinct, nearly consecutive LDS
-//          addresses.  Ranks beyond `kcap` (dense cells) follow in cell order.
+//          and so on, ranked by their place in the cell.  The lanes of a
+//          wave then hold particles of 64 nearby cells, one each, so that the
+//          gather reads and the current atomics of a wave touch distinct, nearly
+//          consecutive LDS addresses.  Ranks beyond `kcap` (dense cells) follow in cell order.
 //          The last arrange block to finish clears the request and counts
 //          the sort.  Between sorts the counts are zero, so a sort needs no
 //          clearing pass, and each of the three kernels reads
@@ -99,11 +99,12 @@ __device__ void scan_counts(const SortArgs<Real>& A, int* part) {
 }
 
 // Count and scatter take kSortItems particles per thread at once, so that a
-// wave waits once for four round trips to memory: the loads, and one atomic
-// per distinct key of the wave, all keys in one instruction.  (One particle
-// per thread and an atomic round trip per distinct key, one after the other:
-// 19M particles in mixed precision 311 and 404 us, 0.87M in FP64 56 and 48 us;
-// now 180 and 322, 23 and 20 us.)
+// wave waits once for four particles' loads.  The lanes of equal keys are found by
+// scalar reads, and there is one atomic per distinct key of the wave, all keys in
+// one instruction; the count's return nothing, the scatter waits for its own once
+// per key set.  (One particle per thread, the keys matched through the LDS and the
+// scatter's atomics one key after the other: 19M particles in mixed precision 311 and
+// 404 us, 0.87M in FP64 56 and 48 us; now 180 and 322, 23 and 20 us.)
 template <class P, int DIM>
 __global__ void __launch_bounds__(kSortBlock) sort_count(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
@@ -533,7 +534,7 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
     } else if (DENSE) {
       // the sources through the tags' place of the current store, which holds
       // nothing yet: 4 bytes of a particle are scattered there, not all of it
-      // (21M particles in mixed precision 2.76 -> 1.57 ms, 21M in FP64 1.40 -> 1.10)
+      // (42M particles in mixed precision 2.76 -> 1.57 ms, 21M in FP64 1.40 -> 1.10)
       for (int i = tid; i < n; i += kArrangeBlock)
         D.tag[s0 + slot_of(cell_in_tile<P, DIM>(S, s0 + i, org, A.tile), A.keys[s0 + i])] = i;
       __syncthreads();
