@@ -104,7 +104,7 @@ __device__ void scan_counts(const SortArgs<Real>& A, int* part) {
 // one instruction; the count's return nothing, the scatter waits for its own once
 // per key set.  (One particle per thread, the keys matched through the LDS and the
 // scatter's atomics one key after the other: 19M particles in mixed precision 311 and
-// 404 us, 0.87M in FP64 56 and 48 us; now 180 and 322, 23 and 20 us.)
+// 404 us, 0.87M in FP64 56 and 48 us; now 140 to 180 and 320, 19 to 23 and 18 to 20 us.)
 template <class P, int DIM>
 __global__ void __launch_bounds__(kSortBlock) sort_count(SortArgs<typename P::Real> A) {
   using Real = typename P::Real;
