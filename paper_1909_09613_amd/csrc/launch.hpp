@@ -32,7 +32,7 @@ struct SortArgs {
   int tile[3];
   int tc;             // cells of a full tile
   int kcap;           // ranks within a cell ordered level by level (arrange pass)
-  int dense;          // most particles lie in segments larger than kArrangeCap
+  int dense;          // most particles lie in segments or cells that are not ordered by place
   int* counts;        // nkeys: particles per segment (zero between sorts)
   int* seg;           // nkeys + 1
   int* keys;          // np_total

@@ -425,13 +425,13 @@ pic_status upload_runs(pic_ctx* c) {
   return c->hip(e, "run table upload");
 }
 
-// Whether most particles belong to runs whose full tiles hold more particles of a
-// species than the sort orders by place within their cells.
+// Whether most particles belong to runs whose cells or full tiles hold more
+// particles of a species than the sort orders by place within their cells.
 bool dense_segments(const pic_ctx* c) {
   const long long cells = (long long)c->tile[0] * c->tile[1] * c->tile[2];
   long long dense = 0;
   for (const RunHost& H : c->runs)
-    if (H.d.ppc_per_species * cells > kArrangeCap) dense += 2 * H.nps;
+    if (H.d.ppc_per_species > kArrangeOrderCount || H.d.ppc_per_species * cells > kArrangeCap) dense += 2 * H.nps;
   return 2 * dense > c->np_total;
 }
 

@@ -321,14 +321,15 @@ __device__ __forceinline__ unsigned order_key(typename P::Real fx, typename P::R
 // 200 us (in groups of 512 the items' 32 registers do not fit).
 // 19M particles in mixed precision 638 -> 477 us, 0.87M in FP64 48 -> 44 us.
 //
-// DENSE: most particles lie in segments of more than kArrangeCap.  All segments
-// take the arrival order, and the keys' place holds as many levels more, since
+// DENSE: most particles lie in segments of more than kArrangeCap, or in cells of
+// more than kArrangeOrderCount.  All segments take the arrival order, and the keys' place holds as many levels more, since
 // ranks beyond the levels lie cell by cell, whole waves in one cell, whose atomics
 // all meet at one address (a longer chain than the levels' random starts).
 // Particle kernel, without -> with the levels in the keys' place (0.45 dx, particles
 // per cell and species): 512x512 cubic FP64 at 40 1153 -> 820 us, quadratic 750 ->
 // 628, cubic at 70 3860 -> 1573; 40^3 linear FP64 at 150 1198 -> 488; 1024x512 cubic
-// mixed at 40 2660 -> 1023; 64^3 quadratic mixed at 70 2500 -> 1266.  (The even
+// mixed at 40 2660 -> 1023; 64^3 quadratic mixed at 70 2500 -> 1266; for the cells alone
+// (smaller segments) 40^3 quadratic FP64 at 100 1336 -> 1098, 32^3 cubic mixed 1305 -> 646.  (The even
 // cells of a row before the odd ones, which pays in arrival order while ranks lie
 // beyond the levels, 1153 -> 1085, does not with them, 628 -> 737.)
 template <class P, int DIM, bool DENSE>

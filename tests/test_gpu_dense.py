@@ -20,6 +20,7 @@ CASES = {
     "fewest-cells": ((9, 8), 1, 520, (4, 4, 1)),
     "ragged-box": ((9, 6, 7), 2, 140, (4, 4, 4)),
     "box-and-more": ((8, 7, 6), 1, 260, (4, 4, 4)),
+    "dense-cells-small-segments": ((17, 12), 2, 70, (8, 8, 1)),
 }
 
 
