@@ -538,6 +538,7 @@ __global__ void __launch_bounds__(kArrangeBlock, 8) sort_arrange(SortArgs<typena
       // (42M particles in mixed precision 2.76 -> 1.57 ms, 21M in FP64 1.40 -> 1.10)
       for (int i = tid; i < n; i += kArrangeBlock)
         D.tag[s0 + slot_of(cell_in_tile<P, DIM>(S, s0 + i, org, A.tile), A.keys[s0 + i])] = i;
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): written before any other wave reads them
       __syncthreads();
       for (int o0 = tid; o0 < n; o0 += W * kArrangeBlock) {
         int src[W];
